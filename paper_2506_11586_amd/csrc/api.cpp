@@ -11,10 +11,15 @@
 
 #include "heconv.h"
 #include "ctx.h"
+#include "pm_form.h"
 #include "kernels.h"
 
 using heconv::LimbConst;
 using heconv::Tw;
+using heconv::TwP;
+using heconv::PmForm;
+using heconv::pm_form;
+using heconv::twp_of;
 using heconv::Geo;
 using heconv::geo_of;
 
@@ -141,11 +146,11 @@ hipError_t ntt_run(const he_ctx* c, bool inverse, uint64_t* polys, uint64_t n, h
     return heconv::ntt_f64_launch(inverse, c->logN, ntt_loge(c, n), polys, n, c->L, inverse ? c->d_inv64 : c->d_fwd64,
                                   c->d_fc, st);
   if (!inverse && n * c->L < c->tune.ntt_split_below && heconv::ntt_fwd_split_supported(c->logN))
-    return heconv::ntt_fwd_split_launch(c->logN, polys, n, c->L, c->d_fwd, c->d_lc, st);
+    return heconv::ntt_fwd_split_launch(c->logN, polys, n, c->L, c->d_fwd, c->d_lc, c->ntt_pm, st);
   if (inverse && n * c->L < c->tune.ntt_inv_split_below && heconv::ntt_inv_split_supported(c->logN))
-    return heconv::ntt_inv_split_launch(c->logN, polys, n, c->L, c->d_inv, c->d_lc, st);
+    return heconv::ntt_inv_split_launch(c->logN, polys, n, c->L, c->d_inv, c->d_lc, c->ntt_pm, st);
   return heconv::ntt_launch(inverse, c->logN, ntt_loge(c, n), polys, n, c->L, inverse ? c->d_inv : c->d_fwd, c->d_lc,
-                            st, nt);
+                            c->ntt_pm, st, nt);
 }
 
 }  // namespace
@@ -194,6 +199,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   }
   c->N = N, c->logN = log2u(N), c->L = L, c->t = prm->t;
   c->q.assign(prm->q, prm->q + L);
+  c->ntt_pm = true;
   const std::vector<uint64_t> dl = deltas(c->q, c->t);
   c->proto_ok = std::all_of(dl.begin(), dl.end(), [](uint64_t v) { return v != 0; });
   std::vector<Tw> fwd((size_t)L * N), inv((size_t)L * N);
@@ -207,6 +213,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     }
     c->psi.push_back(psi);
     const uint64_t psi_inv = mpow(psi, q - 2, q);
+    const bool pm = std::all_of(c->q.begin(), c->q.end(), [](uint64_t v) { return pm_form(v).ok; });
     for (int dir = 0; dir < 2; dir++) {
       const uint64_t base = dir ? psi_inv : psi;
       pw[0] = 1;
@@ -214,7 +221,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
       Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
       for (uint32_t k = 0; k < N; k++) {
         const uint64_t w = pw[bitrev(k, c->logN)];
-        tab[k] = Tw{w, shoup63(w, q)};
+        tab[k] = Tw{w, pm ? 0 : shoup63(w, q)};
       }
     }
     LimbConst k{};
@@ -230,6 +237,14 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     k.three_q = 3 * q, k.neg3q = 0 - 3 * q;
     // the MAC's folds for q = 2^60 - delta, delta < 2^20 (modarith.h, fold30_pm, fold3_pm)
     k.pmd = (q < (1ull << 60) && (1ull << 60) - q < (1ull << 20)) ? (1ull << 60) - q : 0;
+    k.two28 = 1u << 28;
+    const PmForm f = pm_form(q);
+    if (f.ok) {
+      k.pb32 = f.b - 32, k.pmask = (1u << k.pb32) - 1, k.pdelta = f.delta, k.d60 = (int32_t)f.d60;
+      k.pk = q << (63 - f.b);
+      k.pninv = twp_of(k.ninv, q, f.b), k.pninv_w = twp_of(k.ninv_w, q, f.b);
+    }
+    c->ntt_pm &= f.ok;
     c->lc.push_back(k);
   }
   c->all_pm = true;
@@ -266,6 +281,15 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
       heconv::f64_const_fill(fc.data() + heconv::f64_const_size() * l, (double)c->q[l], 1.0 / (double)c->q[l],
                              (double)c->lc[l].ninv, (double)c->lc[l].ninv_w);
   }
+  if (c->ntt_pm)  // the tables of the signed transforms
+    for (uint32_t l = 0; l < L; l++) {
+      const uint32_t b = c->lc[l].pb32 + 32;
+      for (size_t i = (size_t)l * N; i < (size_t)(l + 1) * N; i++)
+        for (Tw* tab : {fwd.data(), inv.data()}) {
+          const TwP p = twp_of(tab[i].w, c->q[l], b);
+          std::memcpy(&tab[i], &p, sizeof(Tw));
+        }
+    }
   const size_t tb = sizeof(Tw) * (size_t)L * N;
   if (hipMalloc(&c->d_fwd, tb) != hipSuccess || hipMalloc(&c->d_inv, tb) != hipSuccess ||
       hipMalloc(&c->d_lc, sizeof(LimbConst) * L) != hipSuccess ||
@@ -459,7 +483,7 @@ he_status he_conv_mac_intt(const he_ctx* c, const he_conv_desc* d, uint32_t B, c
   if (B == 0) return HE_OK;
   if (!d_in_ntt || !d_wntt || !d_out) return HE_EINVAL;
   return dev_err(heconv::mac_intt_launch(c->logN, d_in_ntt, d_wntt, d_out, B, g.CB, g.S, d->M, c->L, c->d_inv,
-                                         c->d_lc, (hipStream_t)stream));
+                                         c->d_lc, c->ntt_pm, (hipStream_t)stream));
 }
 
 he_status he_conv_layer(const he_ctx* c, const he_conv_desc* d, uint32_t B, uint64_t* d_in, const uint64_t* d_wntt,
@@ -662,12 +686,12 @@ he_status ks_run(const he_ctx* ext, uint32_t ginv, uint64_t n, const uint64_t* c
   he_status s = HE_OK;
   const bool fusable = heconv::ks_fwd_supported(ext->logN);
   if (ext->tune.ks_fused == 1 && fusable) {
-    s = dev_err(heconv::modup_ntt_launch(ext->logN, ct, digits, n, L, ginv, ext->d_fwd, ext->d_lc, st));
+    s = dev_err(heconv::modup_ntt_launch(ext->logN, ct, digits, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
     if (!s) s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk, acc, n, L, L, nullptr, nullptr, 0, 0, ext->d_inv,
-                                                  ext->d_lc, st));
+                                                  ext->d_lc, ext->ntt_pm, st));
   } else {
     if (ext->tune.ks_fused == 2 && fusable) {
-      s = dev_err(heconv::ks_fwd_launch(ext->logN, ct, ksk, acc, n, L, ginv, ext->d_fwd, ext->d_lc, st));
+      s = dev_err(heconv::ks_fwd_launch(ext->logN, ct, ksk, acc, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
     } else {
       s = dev_err(heconv::modup_launch(ct, digits, n, N, L, ginv, ext->d_lc, st));
       if (!s) s = dev_err(ntt_run(ext, false, digits, n * L, st));
@@ -829,7 +853,7 @@ he_status he_zp_encode_plain(const he_ctx* ext, uint64_t n, const int64_t* d_coe
                                                      ext->d_lc, st));
     if (s) return s;
   }
-  return dev_err(heconv::ntt_launch(false, ext->logN, ntt_loge(ext, n), d_w, n, L, ext->d_fwd, ext->d_lc, st));
+  return dev_err(heconv::ntt_launch(false, ext->logN, ntt_loge(ext, n), d_w, n, L, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
 }
 
 he_status he_zp_work_words(const he_ctx* ext, uint64_t n, uint64_t* words) {
@@ -877,11 +901,11 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
     const uint32_t i = per - 1 - step;
     uint64_t* next = groups == 1 && step + 1 == per ? d_out : accb[cur];
     he_status s = HE_OK;
-    if (prev) s = dev_err(heconv::modup_ntt_launch(ext->logN, prev, digits, nc, L, ginv, ext->d_fwd, ext->d_lc, st));
+    if (prev) s = dev_err(heconv::modup_ntt_launch(ext->logN, prev, digits, nc, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
     if (!s)
       s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk, sums, nc, L, prev ? L : 0, d_x_ntt,
                                             d_w + (uint64_t)i * L * N, n, (uint64_t)per * L * N, ext->d_inv,
-                                            ext->d_lc, st));
+                                            ext->d_lc, ext->ntt_pm, st));
     if (!s) s = dev_err(heconv::moddown_launch(sums, prev, next, nc, N, L, ginv, pc, ext->d_lc, st));
     if (s) return s;
     prev = next;
@@ -895,10 +919,10 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
   const uint64_t* acc = prev + (uint64_t)(groups - 1) * n * ctw;
   for (uint32_t c = groups - 1; c-- > 0;) {
     uint64_t* next = c == 0 ? d_out : tmp[c & 1];
-    he_status s = dev_err(heconv::modup_ntt_launch(ext->logN, acc, digits, n, L, g2inv, ext->d_fwd, ext->d_lc, st));
+    he_status s = dev_err(heconv::modup_ntt_launch(ext->logN, acc, digits, n, L, g2inv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
     if (!s)
       s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk2, sums, n, L, L, nullptr, nullptr, 0, 0,
-                                            ext->d_inv, ext->d_lc, st));
+                                            ext->d_inv, ext->d_lc, ext->ntt_pm, st));
     if (!s)
       s = dev_err(heconv::moddown_launch(sums, acc, next, n, N, L, g2inv, pc, ext->d_lc, st,
                                          prev + (uint64_t)c * n * ctw));

@@ -11,34 +11,30 @@
 
 namespace heconv {
 
-template <int LOGN, int LOGE>
-__global__ __launch_bounds__((1 << LOGN) >> LOGE) void batch_fwd_kernel(const BatchItem* __restrict__ items,
-                                                                         const BatchJob* __restrict__ jobs,
-                                                                         const Tw* __restrict__ tw,
-                                                                         const LimbConst* __restrict__ lcs,
-                                                                         uint32_t L) {
+template <int LOGN, int LOGE, bool PM>
+__global__ __launch_bounds__((1 << LOGN) >> LOGE, ntt_waves(LOGE)) void batch_fwd_kernel(
+    const BatchItem* __restrict__ items, const BatchJob* __restrict__ jobs, const Tw* __restrict__ tw,
+    const LimbConst* __restrict__ lcs, uint32_t L) {
   constexpr int N = 1 << LOGN;
   __shared__ uint64_t lds[N + N / 16];
   const BatchItem it = items[blockIdx.x];
   gword* in = as_global(jobs[it.job].in);
   const uint32_t l = it.idx % L;
   const LimbConst c = lcs[l];
-  ntt_fwd_poly<LOGN, LOGE>(in + (size_t)it.idx * N, tw + (size_t)l * N, c, lds, threadIdx.x);
+  ntt_fwd_poly<LOGN, LOGE, PM>(in + (size_t)it.idx * N, tw + (size_t)l * N, c, lds, threadIdx.x);
 }
 
-template <int LOGN, int LOGE>
-__global__ __launch_bounds__((1 << LOGN) >> LOGE) void batch_inv_kernel(const BatchItem* __restrict__ items,
-                                                                         const BatchJob* __restrict__ jobs,
-                                                                         const Tw* __restrict__ tw,
-                                                                         const LimbConst* __restrict__ lcs,
-                                                                         uint32_t L) {
+template <int LOGN, int LOGE, bool PM>
+__global__ __launch_bounds__((1 << LOGN) >> LOGE, ntt_waves(LOGE)) void batch_inv_kernel(
+    const BatchItem* __restrict__ items, const BatchJob* __restrict__ jobs, const Tw* __restrict__ tw,
+    const LimbConst* __restrict__ lcs, uint32_t L) {
   constexpr int N = 1 << LOGN;
   __shared__ uint64_t lds[N + N / 16];
   const BatchItem it = items[blockIdx.x];
   gword* out = as_global(jobs[it.job].out);
   const uint32_t l = it.idx % L;
   const LimbConst c = lcs[l];
-  ntt_inv_poly<LOGN, LOGE, true>(out + (size_t)it.idx * N, tw + (size_t)l * N, c, lds, threadIdx.x);
+  ntt_inv_poly<LOGN, LOGE, PM, true>(out + (size_t)it.idx * N, tw + (size_t)l * N, c, lds, threadIdx.x);
 }
 
 // MAC work list: the host interleaves eight per-XCD lists (workgroup b runs
@@ -75,36 +71,39 @@ __global__ __launch_bounds__(BATCH_MAC_THREADS) void batch_mac_stream_kernel(con
   mac_stream<MT, RT, BATCH_MAC_THREADS, P, PM>(src, lcs, L, logN, lds, threadIdx.x);
 }
 
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool PM>
 static void launch_ntt_phase(bool inverse, const BatchPhase& p, const BatchArgs& a, hipStream_t st) {
   constexpr uint32_t T = (1u << LOGN) >> LOGE;
   if (inverse)
-    hipLaunchKernelGGL((batch_inv_kernel<LOGN, LOGE>), dim3(p.n), dim3(T), 0, st, p.items, a.jobs, a.twi, a.lcs, a.L);
+    hipLaunchKernelGGL((batch_inv_kernel<LOGN, LOGE, PM>), dim3(p.n), dim3(T), 0, st, p.items, a.jobs, a.twi, a.lcs,
+                       a.L);
   else
-    hipLaunchKernelGGL((batch_fwd_kernel<LOGN, LOGE>), dim3(p.n), dim3(T), 0, st, p.items, a.jobs, a.twf, a.lcs, a.L);
+    hipLaunchKernelGGL((batch_fwd_kernel<LOGN, LOGE, PM>), dim3(p.n), dim3(T), 0, st, p.items, a.jobs, a.twf, a.lcs,
+                       a.L);
 }
 
-template <int LOGN>
+template <int LOGN, bool PM>
 static hipError_t ntt_phase(bool inverse, uint32_t loge, const BatchPhase& p, const BatchArgs& a, hipStream_t st) {
   if constexpr (LOGN <= 13) {
     if (loge == 3) {
-      launch_ntt_phase<LOGN, 3>(inverse, p, a, st);
+      launch_ntt_phase<LOGN, 3, PM>(inverse, p, a, st);
       return hipGetLastError();
     }
   }
-  launch_ntt_phase<LOGN, 4>(inverse, p, a, st);
+  launch_ntt_phase<LOGN, 4, PM>(inverse, p, a, st);
   return hipGetLastError();
 }
 
+template <bool PM>
 static hipError_t ntt_phase_n(bool inverse, uint32_t logN, uint32_t loge, const BatchPhase& p, const BatchArgs& a,
                               hipStream_t st) {
   if (p.n == 0) return hipSuccess;
   switch (logN) {
-    case 10: return ntt_phase<10>(inverse, loge, p, a, st);
-    case 11: return ntt_phase<11>(inverse, loge, p, a, st);
-    case 12: return ntt_phase<12>(inverse, loge, p, a, st);
-    case 13: return ntt_phase<13>(inverse, loge, p, a, st);
-    case 14: return ntt_phase<14>(inverse, loge, p, a, st);
+    case 10: return ntt_phase<10, PM>(inverse, loge, p, a, st);
+    case 11: return ntt_phase<11, PM>(inverse, loge, p, a, st);
+    case 12: return ntt_phase<12, PM>(inverse, loge, p, a, st);
+    case 13: return ntt_phase<13, PM>(inverse, loge, p, a, st);
+    case 14: return ntt_phase<14, PM>(inverse, loge, p, a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -185,9 +184,12 @@ bool batch_tile_supported(uint32_t mt, uint32_t rt, uint32_t lds) {
 }
 
 hipError_t batch_phase(const BatchChain& ch, const BatchArgs& a, int phase, hipStream_t st) {
-  if (phase == 0) return ntt_phase_n(false, a.logN, ch.fwd.n < 512 ? a.loge_small : a.loge_large, ch.fwd, a, st);
   if (phase == 1) return mac_phase(ch.mac, a, st);
-  return ntt_phase_n(true, a.logN, ch.inv.n < 512 ? a.loge_small : a.loge_large, ch.inv, a, st);
+  const bool inverse = phase == 2;
+  const BatchPhase& p = inverse ? ch.inv : ch.fwd;
+  const uint32_t loge = p.n < 512 ? a.loge_small : a.loge_large;
+  return a.ntt_pm ? ntt_phase_n<true>(inverse, a.logN, loge, p, a, st)
+                  : ntt_phase_n<false>(inverse, a.logN, loge, p, a, st);
 }
 
 hipError_t batch_chain(const BatchChain& ch, const BatchArgs& a, hipStream_t st) {

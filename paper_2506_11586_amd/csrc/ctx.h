@@ -18,8 +18,9 @@ struct he_ctx {
   std::vector<uint64_t> q, psi;
   std::vector<heconv::LimbConst> lc;
   bool all_pm = false;  // every q_l = 2^60 - delta, delta < 2^20
-  heconv::Tw* d_fwd = nullptr;  // [L][N] psi^brv(k) with Shoup quotient
-  heconv::Tw* d_inv = nullptr;  // [L][N] psi^-brv(k) with Shoup quotient
+  bool ntt_pm = false;  // every q_l = 2^b - delta for the signed transforms (modarith.h, pm_mul)
+  heconv::Tw* d_fwd = nullptr;  // [L][N] psi^brv(k) with Shoup quotient (ntt_pm: TwP entries)
+  heconv::Tw* d_inv = nullptr;  // [L][N] psi^-brv(k) likewise
   heconv::LimbConst* d_lc = nullptr;
   heconv::DecodeConst* d_dc = nullptr;  // client-side decoding constants (t a power of two)
   // double-precision transforms (every q_l < 2^50)

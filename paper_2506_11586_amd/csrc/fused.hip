@@ -19,7 +19,7 @@ constexpr int FUSED_E = 16;     // NTT points per thread (the inverse NTT's 16-w
 constexpr int FUSED_G = 4;      // points accumulated per MAC pass
 constexpr int FUSED_DEPTH = 2;  // channel blocks whose loads are issued together
 
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ __launch_bounds__((1 << LOGN) / FUSED_E, 4) void mac_intt_kernel(const uint64_t* __restrict__ in_,
                                                                           const uint64_t* __restrict__ w_,
                                                                           uint64_t* __restrict__ out_, uint32_t B,
@@ -93,31 +93,38 @@ __global__ __launch_bounds__((1 << LOGN) / FUSED_E, 4) void mac_intt_kernel(cons
     for (int e = 0; e < G; e++) x[g0 + e] = res[e];
   }
   // x holds the NTT-form output in the top mapping (point tid + k*T)
-  ntt_inv_regs<LOGN, 4>(x, twi + (size_t)l * N, c, lds, tid);
+  ntt_inv_regs<LOGN, 4, PM>(x, twi + (size_t)l * N, c, lds, tid);
   gword* op = out + ((((uint64_t)b * M + m) * S + s) * 2 + comp) * LN + (uint64_t)l * N + tid;
 #pragma unroll
   for (int k = 0; k < E; k++) op[k * T] = x[k];
 }
 
-template <int LOGN>
-static hipError_t go(const uint64_t* in, const uint64_t* w, uint64_t* out, uint32_t B, uint32_t CB, uint32_t S,
+template <int LOGN, bool PM>
+static hipError_t go_pm(const uint64_t* in, const uint64_t* w, uint64_t* out, uint32_t B, uint32_t CB, uint32_t S,
                      uint32_t M, uint32_t L, const Tw* twi, const LimbConst* lc, hipStream_t st) {
   const uint64_t blocks = (uint64_t)B * S * 2 * M * L;
   if (blocks > grid_max_blocks((1u << LOGN) / FUSED_E)) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((mac_intt_kernel<LOGN>), dim3((uint32_t)blocks), dim3((1 << LOGN) / FUSED_E), 0, st,
+  hipLaunchKernelGGL((mac_intt_kernel<LOGN, PM>), dim3((uint32_t)blocks), dim3((1 << LOGN) / FUSED_E), 0, st,
                      in, w, out, B, CB, S, M, L, twi, lc);
   return hipGetLastError();
 }
 
+template <int LOGN>
+static hipError_t go(const uint64_t* in, const uint64_t* w, uint64_t* out, uint32_t B, uint32_t CB, uint32_t S,
+                     uint32_t M, uint32_t L, const Tw* twi, const LimbConst* lc, bool pm, hipStream_t st) {
+  return pm ? go_pm<LOGN, true>(in, w, out, B, CB, S, M, L, twi, lc, st)
+            : go_pm<LOGN, false>(in, w, out, B, CB, S, M, L, twi, lc, st);
+}
+
 hipError_t mac_intt_launch(uint32_t logN, const uint64_t* in, const uint64_t* w, uint64_t* out, uint32_t B,
                            uint32_t CB, uint32_t S, uint32_t M, uint32_t L, const Tw* twi, const LimbConst* lc,
-                           hipStream_t st) {
+                           bool pm, hipStream_t st) {
   switch (logN) {
-    case 10: return go<10>(in, w, out, B, CB, S, M, L, twi, lc, st);
-    case 11: return go<11>(in, w, out, B, CB, S, M, L, twi, lc, st);
-    case 12: return go<12>(in, w, out, B, CB, S, M, L, twi, lc, st);
-    case 13: return go<13>(in, w, out, B, CB, S, M, L, twi, lc, st);
-    case 14: return go<14>(in, w, out, B, CB, S, M, L, twi, lc, st);
+    case 10: return go<10>(in, w, out, B, CB, S, M, L, twi, lc, pm, st);
+    case 11: return go<11>(in, w, out, B, CB, S, M, L, twi, lc, pm, st);
+    case 12: return go<12>(in, w, out, B, CB, S, M, L, twi, lc, pm, st);
+    case 13: return go<13>(in, w, out, B, CB, S, M, L, twi, lc, pm, st);
+    case 14: return go<14>(in, w, out, B, CB, S, M, L, twi, lc, pm, st);
     default: return hipErrorInvalidValue;
   }
 }

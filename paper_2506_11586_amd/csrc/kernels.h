@@ -14,10 +14,12 @@ constexpr uint64_t grid_max_blocks(uint32_t threads) { return 0xffffffffull / th
 
 // Forward (inverse = false) or inverse NTT, in place, of n_rns_polys RNS
 // polynomials [n][L][N], N = 2^logN, logN in [10, 14]; 2^loge words per
-// thread (loge 3 or 4; 3 needs logN <= 13, else 4 is used).  nt: the
-// inverse transform stores its result non-temporally (a layer's output).
+// thread (loge 3 or 4; 3 needs logN <= 13, else 4 is used).  pm: the tables
+// are of the signed transforms (TwP entries; modarith.h, pm_mul), here and in
+// every launcher below.  nt: the inverse transform stores its result
+// non-temporally (a layer's output).
 hipError_t ntt_launch(bool inverse, uint32_t logN, uint32_t loge, uint64_t* polys, uint64_t n_rns_polys, uint32_t L,
-                      const Tw* tw, const LimbConst* lc, hipStream_t st, bool nt = false);
+                      const Tw* tw, const LimbConst* lc, bool pm, hipStream_t st, bool nt = false);
 
 // Forward NTT in two grids (first six stages by residue class, the rest by
 // block), for counts too small to occupy every compute unit; logN 12..14.
@@ -25,9 +27,9 @@ bool ntt_fwd_split_supported(uint32_t logN);
 // the inverse in two grids (N = 2^13, 2^14)
 bool ntt_inv_split_supported(uint32_t logN);
 hipError_t ntt_inv_split_launch(uint32_t logN, uint64_t* polys, uint64_t n_rns_polys, uint32_t L, const Tw* tw,
-                                const LimbConst* lc, hipStream_t st);
+                                const LimbConst* lc, bool pm, hipStream_t st);
 hipError_t ntt_fwd_split_launch(uint32_t logN, uint64_t* polys, uint64_t n_rns_polys, uint32_t L, const Tw* tw,
-                                const LimbConst* lc, hipStream_t st);
+                                const LimbConst* lc, bool pm, hipStream_t st);
 
 // NTT / inverse NTT in double precision (every q_l < 2^50): tw are the
 // twiddles as doubles ([L][N], forward or inverse table), fc the per-limb
@@ -52,12 +54,12 @@ hipError_t moddown_launch(const uint64_t* acc, const uint64_t* ct, uint64_t* out
                           const uint64_t* addp = nullptr);
 bool ks_fwd_supported(uint32_t logN);
 hipError_t ks_fwd_launch(uint32_t logN, const uint64_t* ct, const uint64_t* ksk, uint64_t* acc, uint64_t n, uint32_t L,
-                         uint32_t ginv, const Tw* tw, const LimbConst* ext, hipStream_t st);
+                         uint32_t ginv, const Tw* tw, const LimbConst* ext, bool pm, hipStream_t st);
 hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits, uint64_t n, uint32_t L, uint32_t ginv,
-                            const Tw* tw, const LimbConst* ext, hipStream_t st);
+                            const Tw* tw, const LimbConst* ext, bool pm, hipStream_t st);
 hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
                              uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
-                             uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, hipStream_t st);
+                             uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, bool pm, hipStream_t st);
 hipError_t galois_key_launch(const uint64_t* work, uint64_t* ksk, uint32_t N, uint32_t L, const LimbConst* ext,
                              hipStream_t st);
 
@@ -114,7 +116,7 @@ inline bool mac_dma_fits(uint32_t CB, uint32_t L, uint32_t N) {
 // Fused MAC + inverse NTT: in (NTT form) x w -> out (coefficient form).
 hipError_t mac_intt_launch(uint32_t logN, const uint64_t* in, const uint64_t* w, uint64_t* out, uint32_t B,
                            uint32_t CB, uint32_t S, uint32_t M, uint32_t L, const Tw* twi, const LimbConst* lc,
-                           hipStream_t st);
+                           bool pm, hipStream_t st);
 
 // Geometry of the protocol steps around a layer (conv, packing, tiling).
 struct ProtoGeom {

@@ -10,6 +10,13 @@
 
 namespace heconv {
 
+// A factor w of the signed transforms (pm_mul): w = w0 + w1 * 2^28 and
+// w * 2^32 mod q = v0 + v1 * 2^28, all four signed words.  The same size as
+// Tw, whose place it takes in the twiddle tables.
+struct TwP {
+  int32_t w0, w1, v0, v1;
+};
+
 // Per-limb constants kept on the device.
 struct LimbConst {
   uint64_t q, two_q;
@@ -24,6 +31,13 @@ struct LimbConst {
   uint64_t r64_sh63;           // Shoup quotient of 2^64 mod q at scale 2^63
   uint64_t pmd;                // delta when q = 2^60 - delta with delta < 2^20, else 0
   uint64_t three_q, neg3q;     // 3q and 2^64 - 3q (the inverse transform's lazy bound)
+  // q = 2^pb - pdelta with a small pdelta (the signed transforms, see pm_mul):
+  uint32_t pb32, pmask;        // pb - 32, and the mask of a word's bits from 32 up below bit pb
+  uint32_t pdelta, two28;      // pdelta, 2^28
+  int32_t d60;                 // 2^60 mod q = pdelta * 2^(60 - pb)
+  uint32_t pad_;
+  uint64_t pk;                 // 2^(63 - pb) * q, the multiple of q next below 2^63
+  TwP pninv, pninv_w;          // N^-1 and N^-1 * (last inverse twiddle)
 };
 
 // Device buffers are passed to the transform and MAC bodies as pointers in
@@ -124,6 +138,89 @@ __device__ __forceinline__ uint64_t reduce128(uint64_t hi, uint64_t lo, const Li
   uint64_t s = a + b;                                     // [0, 4q) < 2^63
   s = csub(s, c.two_q);
   return csub(s, c.q);
+}
+
+// ---------------------------------------------------------------------------
+// Signed arithmetic of the transforms for q = 2^pb - delta, delta < 2^24 and
+// d60 = delta * 2^(60 - pb) < 2^31 (every prime that he_gen_primes finds near
+// the top of its range).  A value is any signed 64-bit integer of its residue
+// class; bounds below are in units of u = 2^60.
+//
+// pm_mul: x = xs0 + xs1 * 2^32 with both words signed, times the factor
+// (w, v), |w|, |v| < 2^59:
+//   x*w = xs0*w + xs1*v = A + 2^28 * B  (mod q),
+//   A = xs0*w0 + xs1*v0,  B = xs0*w1 + xs1*v1 (|B| < 2^63),
+// and with B = Bl + 2^32 * Bh, 2^60 * Bh = d60 * Bh: the split at bit 28
+// makes B's two words the two parts that the reduction needs, so a product
+// is six multiply-adds (the quotient form mul_shoup_2q takes ten multiplies).
+// 2^31 is added to B and 2^59 taken from A, which centres Bl:
+//   |result| < 0.25u + |x|/32 + 0.5u + delta * (2^30 + |x|/2^33)
+//           <= T(|x|) = 0.766u + 0.0333|x|.
+// Butterflies then need no conditional subtraction: sums and differences stay
+// signed, and pm_red brings a value to 0.5u where a bound would reach 7.5u.
+// ---------------------------------------------------------------------------
+
+// The constants of pm_mul in registers: c1 = -2^59, c2 = 2^31 (hidden from
+// the compiler, which would otherwise add them in instructions of their own).
+struct PmRegs {
+  int64_t c1, c2;
+  uint32_t two28;
+  int32_t d60;
+};
+
+__host__ __device__ __forceinline__ PmRegs pm_regs(const LimbConst& c) {
+  PmRegs r{-(1ll << 59), 1ll << 31, c.two28, c.d60};
+#ifdef __HIP_DEVICE_COMPILE__
+  __asm__("" : "+v"(r.c1), "+v"(r.c2));
+#endif
+  return r;
+}
+
+__host__ __device__ __forceinline__ uint64_t pm_mul(int32_t xs0, int32_t xs1, const TwP& t, const PmRegs& k) {
+  int64_t A = (int64_t)xs0 * t.w0 + k.c1;
+  int64_t B = (int64_t)xs0 * t.w1 + k.c2;
+  A = (int64_t)xs1 * t.v0 + A;
+  B = (int64_t)xs1 * t.v1 + B;
+#ifdef __HIP_DEVICE_COMPILE__
+  __asm__("" : "+v"(A), "+v"(B));  // keeps the multiply-adds a chain
+#endif
+  uint64_t R = (uint64_t)(uint32_t)B * k.two28 + (uint64_t)A;
+#ifdef __HIP_DEVICE_COMPILE__
+  __asm__("" : "+v"(R));
+#endif
+  return (uint64_t)((int64_t)(int32_t)(B >> 32) * k.d60) + R;
+}
+
+// x as its two signed words: the low word's sign is carried into the high one.
+__host__ __device__ __forceinline__ uint64_t pm_mul_val(uint64_t x, const TwP& t, const PmRegs& k) {
+  const uint32_t lo = (uint32_t)x;
+  return pm_mul((int32_t)lo, (int32_t)((uint32_t)(x >> 32) + (lo >> 31)), t, k);
+}
+
+// A value stored as x + 2^31: its high word is xs1 already, its low word's
+// top bit flipped is xs0.
+__host__ __device__ __forceinline__ uint64_t pm_mul_biased(uint64_t y, const TwP& t, const PmRegs& k) {
+  return pm_mul((int32_t)((uint32_t)y ^ 0x80000000u), (int32_t)(y >> 32), t, k);
+}
+
+// |x| < 7.5u brought to |x| <= 0.5u + 8 * d60.
+__host__ __device__ __forceinline__ uint64_t pm_red(uint64_t x, const PmRegs& k) {
+  const uint32_t hi = (uint32_t)(x >> 32);
+  const int32_t e = (int32_t)(hi + (1u << 27)) >> 28;
+  const int32_t h = (int32_t)(hi << 4) >> 4;
+  return (uint64_t)((int64_t)e * k.d60) + (((uint64_t)(uint32_t)h << 32) | (uint32_t)x);
+}
+
+// The canonical residue of z = x + pk (as unsigned) for |x| < 7.9u:
+// z = r + e * 2^pb = r + e * delta = y < 2^pb + 2^(64 - pb) * delta < 2q,
+// and y >= q exactly when y + delta has bit pb.
+__host__ __device__ __forceinline__ uint64_t pm_canon(uint64_t z, const LimbConst& c) {
+  const uint32_t hi = (uint32_t)(z >> 32);
+  const uint64_t r = ((uint64_t)(hi & c.pmask) << 32) | (uint32_t)z;
+  const uint64_t y = (uint64_t)(hi >> c.pb32) * c.pdelta + r;
+  const uint32_t ge = (uint32_t)((y + c.pdelta) >> 32) >> c.pb32;
+  const uint64_t o = (uint64_t)ge * c.pdelta + y;
+  return ((uint64_t)((uint32_t)(o >> 32) & c.pmask) << 32) | (uint32_t)o;
 }
 
 // Residues below 2^60 split into 30-bit halves: x = hi*2^30 + lo.  Products

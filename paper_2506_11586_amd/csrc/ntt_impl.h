@@ -15,6 +15,12 @@
 // mul_shoup_2q).  Every stored word is canonical (fwd_canon, or the last
 // inverse stage).
 //
+// With PM (every prime 2^b - delta with small delta: modarith.h, pm_mul) both
+// directions work on signed values instead, with no conditional subtraction
+// in a butterfly; fwd_pass and inv_pass state where pm_red is needed.  The
+// words stored are the same canonical residues.  VALU cycles of a butterfly
+// at full rate: 38 forward and about 45 inverse, against 84.
+//
 // Thread/element mapping of a pass over bits [lo, lo+LOGE): register k of
 // thread t holds element j = (t mod 2^lo) | k << lo | (t >> lo) << (lo+LOGE).
 // The top pass (lo = n-LOGE) is j = t + k*N/E: global loads and stores use
@@ -28,6 +34,11 @@
 
 
 namespace heconv {
+
+// Waves per SIMD that the register budget must allow: two workgroups of 1024
+// threads per CU with 8 words per thread (64 VGPRs; without the bound the
+// signed inverse took 70 and ran one), one with 16.
+constexpr int ntt_waves(int loge) { return loge == 3 ? 8 : 4; }
 
 __device__ __forceinline__ int lds_pad(int j) { return j + (j >> 4); }
 
@@ -55,41 +66,100 @@ __device__ __forceinline__ uint64_t fwd_canon(uint64_t x, const LimbConst& c) {
   return canon_below6q(x, c.neg3q, c.neg2q, c.negq);
 }
 
+// Forward values of the PM form are stored with a bias of 2^31 (pm_mul_biased);
+// the bias passes through X + T and X - T unchanged.  A loaded word gets it
+// here, and fwd_canon takes it off.
+template <bool PM>
+__device__ __forceinline__ uint64_t fwd_in(uint64_t x) {
+  return PM ? x + (1ull << 31) : x;
+}
+
+// A forward value (below 6q; PM: |x| < 7.9u, biased) brought to [0, q).
+template <bool PM>
+__device__ __forceinline__ uint64_t fwd_canon(uint64_t x, const LimbConst& c) {
+  if constexpr (PM)
+    return pm_canon(x + (c.pk - (1ull << 31)), c);
+  else
+    return canon_below6q(x, c.neg3q, c.neg2q, c.negq);
+}
+
 // Forward stages u in [U0, LOGE) of the pass at bit offset LO.  jb: index
 // of the workgroup's first element when it transforms a block of a longer
 // polynomial (the stages on bits below the block size only; jb a multiple of
 // the block size), else 0.
-template <int LOGN, int LOGE, int LO, int U0>
+// PM: a stage takes a bound of a to a + T(a), so canonical inputs (1u) reach
+// 7.2u after seven stages, and values brought to 0.5u 7.54u after eight; RED
+// brings them there before the pass (fwd_red).
+template <int LOGN, int LOGE, int LO, int U0, bool PM, bool RED = false>
 __device__ __forceinline__ void fwd_pass(uint64_t (&x)[1 << LOGE], int tid, const Tw* __restrict__ tw,
-                                         const LimbConst& c, uint32_t jb = 0) {
+                                         const LimbConst& c, const PmRegs& pk, uint32_t jb = 0) {
   const int high = block_of<LO>(tid);
   const uint64_t q3 = c.three_q;
+  if constexpr (PM && RED) {
+#pragma unroll
+    for (int k = 0; k < (1 << LOGE); k++) x[k] = pm_red(x[k], pk);
+  }
 #pragma unroll
   for (int u = U0; u < LOGE; u++) {
     const int s = LOGN - LOGE - LO + u;  // stage index: butterflies on bit LO+LOGE-1-u
     const int half = 1 << (LOGE - 1 - u);
 #pragma unroll
     for (int g = 0; g < (1 << u); g++) {
-      const Tw t = tw[(1 << s) + (jb >> (LO + LOGE - u)) + (high << u) + g];
+      const uint32_t ti = (1 << s) + (jb >> (LO + LOGE - u)) + (high << u) + g;
+      if constexpr (PM) {
+        const TwP t = reinterpret_cast<const TwP*>(tw)[ti];
 #pragma unroll
-      for (int e = 0; e < half; e++) {
-        const int k0 = g * 2 * half + e, k1 = k0 + half;
-        const uint64_t X = csub_neg(x[k0], c.neg3q);
-        const uint64_t T = mul_shoup_2q(x[k1], t.w, t.wsh, c.neg2q);
-        x[k0] = X + T;
-        x[k1] = X - T + q3;
+        for (int e = 0; e < half; e++) {
+          const int k0 = g * 2 * half + e, k1 = k0 + half;
+          const uint64_t X = x[k0], T = pm_mul_biased(x[k1], t, pk);
+          x[k0] = X + T;
+          x[k1] = X - T;
+        }
+      } else {
+        const Tw t = tw[ti];
+#pragma unroll
+        for (int e = 0; e < half; e++) {
+          const int k0 = g * 2 * half + e, k1 = k0 + half;
+          const uint64_t X = csub_neg(x[k0], c.neg3q);
+          const uint64_t T = mul_shoup_2q(x[k1], t.w, t.wsh, c.neg2q);
+          x[k0] = X + T;
+          x[k1] = X - T + q3;
+        }
       }
     }
   }
+}
+
+// Whether the forward full pass P (stages LOGE*P ..) first brings its values
+// to 0.5u: when the stages since the last time, with its own, exceed seven.
+// fwd_since: stages since then, before pass P.
+template <int LOGE>
+constexpr int fwd_since(int P) {
+  int since = 0;
+  for (int p = 0; p < P; p++) {
+    if (since + LOGE > 7) since = 0;
+    since += LOGE;
+  }
+  return since;
 }
 
 // Inverse stages u from LOGE-1 down to U0 of the pass at LO.  With LAST, the
 // stage on the top bit (u = 0 of the pass at n-LOGE) also applies N^-1 and
 // leaves canonical values.  jb as in fwd_pass (a block's first element, for
 // the stages on bits below the block size; never with LAST).
-template <int LOGN, int LOGE, int LO, int U0, bool LAST>
+//
+// PM: with s and p for the sum and the product of a stage, an input bound a
+// <= 1.8u gives after two stages ss 4a = 7.2u, sp T(4a) = 1.0u, ps 2T(2a) =
+// 1.77u, pp 0.83u; ss is then brought to 0.5u.  After three: sss 1.0u, ssp
+// 0.8u, sps 2.0u, spp 0.84u, pss 3.5u, psp 0.89u, pps 1.65u, ppp 0.83u; sps
+// and pss are brought to 0.5u.  After four: ssss 2.0u, ppss 3.3u, both
+// brought to 0.5u, and no other above 1.77u.  A pass of one stage on
+// canonical inputs brings its sums (2u) to 0.5u.  So every pass starts below
+// 1.8u again, and no value reaches 7.5u.  Register k's bit j is 0 where
+// stage j of the pass left it a sum.
+template <int LOGN, int LOGE, int LO, int U0, bool LAST, bool PM>
 __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], int tid, const Tw* __restrict__ tw,
-                                         const LimbConst& c, uint32_t jb = 0) {
+                                         const LimbConst& c, const PmRegs& pk, uint32_t jb = 0) {
   const int high = block_of<LO>(tid);
   const uint64_t q3 = c.three_q;
 #pragma unroll
@@ -101,20 +171,46 @@ __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], int tid, cons
       for (int e = 0; e < half; e++) {
         const int k0 = e, k1 = e + half;
         uint64_t X = x[k0], Y = x[k1];
-        x[k0] = csub_neg(mul_shoup_neg(X + Y, c.ninv, c.ninv_sh, c.negq), c.negq);
-        x[k1] = csub_neg(mul_shoup_neg(X - Y + q3, c.ninv_w, c.ninv_w_sh, c.negq), c.negq);
+        if constexpr (PM) {
+          x[k0] = pm_canon(pm_mul_val(X + Y, c.pninv, pk) + c.pk, c);
+          x[k1] = pm_canon(pm_mul_val(X - Y, c.pninv_w, pk) + c.pk, c);
+        } else {
+          x[k0] = csub_neg(mul_shoup_neg(X + Y, c.ninv, c.ninv_sh, c.negq), c.negq);
+          x[k1] = csub_neg(mul_shoup_neg(X - Y + q3, c.ninv_w, c.ninv_w_sh, c.negq), c.negq);
+        }
       }
       continue;
     }
 #pragma unroll
     for (int g = 0; g < (1 << u); g++) {
-      const Tw t = tw[(1 << s) + (jb >> (LO + LOGE - u)) + (high << u) + g];
+      const uint32_t ti = (1 << s) + (jb >> (LO + LOGE - u)) + (high << u) + g;
+      if constexpr (PM) {
+        const TwP t = reinterpret_cast<const TwP*>(tw)[ti];
 #pragma unroll
-      for (int e = 0; e < half; e++) {
-        const int k0 = g * 2 * half + e, k1 = k0 + half;
-        uint64_t X = x[k0], Y = x[k1];
-        x[k0] = csub_neg(X + Y, c.neg3q);
-        x[k1] = mul_shoup_2q(X - Y + q3, t.w, t.wsh, c.neg2q);
+        for (int e = 0; e < half; e++) {
+          const int k0 = g * 2 * half + e, k1 = k0 + half;
+          const uint64_t X = x[k0], Y = x[k1];
+          x[k0] = X + Y;
+          x[k1] = pm_mul_val(X - Y, t, pk);
+        }
+      } else {
+        const Tw t = tw[ti];
+#pragma unroll
+        for (int e = 0; e < half; e++) {
+          const int k0 = g * 2 * half + e, k1 = k0 + half;
+          uint64_t X = x[k0], Y = x[k1];
+          x[k0] = csub_neg(X + Y, c.neg3q);
+          x[k1] = mul_shoup_2q(X - Y + q3, t.w, t.wsh, c.neg2q);
+        }
+      }
+    }
+    if constexpr (PM) {
+      const int j = LOGE - u;  // stages done
+#pragma unroll
+      for (int k = 0; k < (1 << LOGE); k++) {
+        const bool r = (j == 1 && U0 == LOGE - 1 && (k & 1) == 0) || (j == 2 && (k & 3) == 0) ||
+                       (j == 3 && ((k & 7) == 1 || (k & 7) == 2)) || (j == 4 && ((k & 15) == 0 || (k & 15) == 3));
+        if (r) x[k] = pm_red(x[k], pk);
       }
     }
   }
@@ -155,49 +251,62 @@ __device__ __forceinline__ void exchange(uint64_t* lds, uint64_t (&x)[1 << LOGE]
 }
 
 // Forward full passes at LO = LOGN-LOGE*(P+1), then the partial pass.
-template <int LOGN, int LOGE, int P>
+template <int LOGN, int LOGE, int P, bool PM>
 __device__ __forceinline__ void fwd_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds, int tid,
-                                         const Tw* __restrict__ tw, const LimbConst& c) {
+                                         const Tw* __restrict__ tw, const LimbConst& c, const PmRegs& pk) {
   constexpr int NFULL = LOGN / LOGE, REM = LOGN % LOGE;
   if constexpr (P < NFULL) {
     constexpr int LO = LOGN - LOGE * (P + 1);
     if constexpr (P > 0) exchange<LOGE, LO + LOGE, LO>(lds, x, tid);
-    fwd_pass<LOGN, LOGE, LO, 0>(x, tid, tw, c);
-    fwd_rest<LOGN, LOGE, P + 1>(x, lds, tid, tw, c);
+    fwd_pass<LOGN, LOGE, LO, 0, PM, (fwd_since<LOGE>(P) + LOGE > 7)>(x, tid, tw, c, pk);
+    fwd_rest<LOGN, LOGE, P + 1, PM>(x, lds, tid, tw, c, pk);
   } else if constexpr (REM > 0) {
     exchange<LOGE, LOGN - LOGE * NFULL, 0>(lds, x, tid);
-    fwd_pass<LOGN, LOGE, 0, LOGE - REM>(x, tid, tw, c);
+    fwd_pass<LOGN, LOGE, 0, LOGE - REM, PM, (fwd_since<LOGE>(NFULL) + REM > 7)>(x, tid, tw, c, pk);
   }
 }
 
 // Inverse full passes at LO = REM + LOGE*P (the partial pass at LO = 0, if
 // any, has already run).
-template <int LOGN, int LOGE, int P>
+template <int LOGN, int LOGE, int P, bool PM>
 __device__ __forceinline__ void inv_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds, int tid,
-                                         const Tw* __restrict__ tw, const LimbConst& c) {
+                                         const Tw* __restrict__ tw, const LimbConst& c, const PmRegs& pk) {
   constexpr int NFULL = LOGN / LOGE, REM = LOGN % LOGE;
   if constexpr (P < NFULL) {
     constexpr int LO = REM + LOGE * P;
     constexpr int PREV = (P == 0) ? 0 : REM + LOGE * (P - 1);
     if constexpr (P > 0 || REM > 0) exchange<LOGE, PREV, LO>(lds, x, tid);
-    inv_pass<LOGN, LOGE, LO, 0, (P == NFULL - 1)>(x, tid, tw, c);
-    inv_rest<LOGN, LOGE, P + 1>(x, lds, tid, tw, c);
+    inv_pass<LOGN, LOGE, LO, 0, (P == NFULL - 1), PM>(x, tid, tw, c, pk);
+    inv_rest<LOGN, LOGE, P + 1, PM>(x, lds, tid, tw, c, pk);
   }
+}
+
+// Forward transform of values in registers in the top mapping (register k of
+// thread t = entry t + k*N/E; canonical, PM: any below 2^60), left canonical
+// in the same mapping.
+template <int LOGN, int LOGE, bool PM>
+__device__ __forceinline__ void ntt_fwd_regs(uint64_t (&x)[1 << LOGE], const Tw* __restrict__ tw, const LimbConst& c,
+                                             uint64_t* lds, int tid) {
+  constexpr int E = 1 << LOGE, TOP = LOGN - LOGE;
+  const PmRegs pk = pm_regs(c);
+#pragma unroll
+  for (int k = 0; k < E; k++) x[k] = fwd_in<PM>(x[k]);
+  fwd_rest<LOGN, LOGE, 0, PM>(x, lds, tid, tw, c, pk);
+#pragma unroll
+  for (int k = 0; k < E; k++) x[k] = fwd_canon<PM>(x[k], c);
+  exchange<LOGE, 0, TOP>(lds, x, tid);
 }
 
 // Forward transform of one limb polynomial a[N] (in place) by the calling
 // workgroup of N/2^LOGE threads.
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool PM>
 __device__ __forceinline__ void ntt_fwd_poly(gword* __restrict__ a, const Tw* __restrict__ tw, const LimbConst& c,
                                              uint64_t* lds, int tid) {
-  constexpr int N = 1 << LOGN, E = 1 << LOGE, T = N / E, TOP = LOGN - LOGE;
+  constexpr int N = 1 << LOGN, E = 1 << LOGE, T = N / E;
   uint64_t x[E];
 #pragma unroll
   for (int k = 0; k < E; k++) x[k] = a[tid + k * T];
-  fwd_rest<LOGN, LOGE, 0>(x, lds, tid, tw, c);
-#pragma unroll
-  for (int k = 0; k < E; k++) x[k] = fwd_canon(x[k], c);
-  exchange<LOGE, 0, TOP>(lds, x, tid);  // back to j = tid + k*T for a coalesced store
+  ntt_fwd_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);  // back to j = tid + k*T for a coalesced store
 #pragma unroll
   for (int k = 0; k < E; k++) a[tid + k * T] = x[k];
 }
@@ -205,20 +314,21 @@ __device__ __forceinline__ void ntt_fwd_poly(gword* __restrict__ a, const Tw* __
 // Inverse transform of NTT values already in registers in the top mapping
 // (register k of thread t = entry t + k*N/E); leaves the coefficients, in
 // the same mapping, canonical.
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool PM>
 __device__ __forceinline__ void ntt_inv_regs(uint64_t (&x)[1 << LOGE], const Tw* __restrict__ tw, const LimbConst& c,
                                              uint64_t* lds, int tid) {
   constexpr int TOP = LOGN - LOGE, REM = LOGN % LOGE;
+  const PmRegs pk = pm_regs(c);
   exchange<LOGE, TOP, 0>(lds, x, tid);
-  if constexpr (REM > 0) inv_pass<LOGN, LOGE, 0, LOGE - REM, false>(x, tid, tw, c);
-  inv_rest<LOGN, LOGE, 0>(x, lds, tid, tw, c);
+  if constexpr (REM > 0) inv_pass<LOGN, LOGE, 0, LOGE - REM, false, PM>(x, tid, tw, c, pk);
+  inv_rest<LOGN, LOGE, 0, PM>(x, lds, tid, tw, c, pk);
 }
 
 // Inverse transform of one limb polynomial a[N] (in place).  With NT the
 // input is loaded and the result stored non-temporally: a layer's MAC output
 // is read once here, and its result is not read again soon, so streaming
 // both past the caches keeps L2 and the Infinity Cache for the weights.
-template <int LOGN, int LOGE, bool NT = false>
+template <int LOGN, int LOGE, bool PM, bool NT = false>
 __device__ __forceinline__ void ntt_inv_poly(gword* __restrict__ a, const Tw* __restrict__ tw, const LimbConst& c,
                                              uint64_t* lds, int tid) {
   constexpr int N = 1 << LOGN, E = 1 << LOGE, T = N / E;
@@ -230,7 +340,7 @@ __device__ __forceinline__ void ntt_inv_poly(gword* __restrict__ a, const Tw* __
     else
       x[k] = a[tid + k * T];
   }
-  ntt_inv_regs<LOGN, LOGE>(x, tw, c, lds, tid);
+  ntt_inv_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);
 #pragma unroll
   for (int k = 0; k < E; k++) {
     if constexpr (NT)

@@ -148,13 +148,13 @@ __global__ __launch_bounds__(ROT_THREADS) void moddown_kernel(const uint64_t* __
 // in registers and only they are stored.  The L+1 workgroups of one
 // ciphertext run on the same XCD (block b runs on XCD b % 8), so they share
 // its a rows in that XCD's L2.  Grid: ceil(n/8)*8*(L+1) workgroups.
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ __launch_bounds__((1 << LOGN) >> 3) void ks_fwd_kernel(const uint64_t* __restrict__ ct,
                                                                    const uint64_t* __restrict__ ksk,
                                                                    uint64_t* __restrict__ acc, uint64_t n, uint32_t L,
                                                                    uint32_t ginv, const Tw* __restrict__ tw_all,
                                                                    const LimbConst* __restrict__ ext) {
-  constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E, TOP = LOGN - LOGE;
+  constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E;
   __shared__ uint64_t lds[N + N / 16];
   const uint32_t L1 = L + 1;
   const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
@@ -192,14 +192,11 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void ks_fwd_kernel(const uint64_t
         x[k] = src >= (uint32_t)N && v ? ql - v : v;
       }
     }
-    if (m != l) {
+    if (!PM && m != l) {  // (PM: the transform takes any word below 2^60)
 #pragma unroll
       for (int k = 0; k < E; k++) x[k] = red_word(x[k], c);
     }
-    fwd_rest<LOGN, LOGE, 0>(x, lds, tid, tw, c);
-#pragma unroll
-    for (int k = 0; k < E; k++) x[k] = fwd_canon(x[k], c);
-    exchange<LOGE, 0, TOP>(lds, x, tid);  // entry tid + k*T, as the key rows are read
+    ntt_fwd_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);  // entry tid + k*T, as the key rows are read
     // the key loads are addressed from a value defined here, so they are
     // issued after the transform rather than held in registers through it
     int tk = tid;
@@ -230,13 +227,13 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void ks_fwd_kernel(const uint64_t
 // automorphism, staged in LDS as in ks_fwd_kernel), reduces it mod p_m and
 // stores its transform to digits[i][l][m].  The L+1 workgroups that read one
 // a row run on the same XCD.  Grid: ceil(n*L/8)*8*(L+1) workgroups.
-template <int LOGN>
-__global__ __launch_bounds__((1 << LOGN) >> 3) void modup_ntt_kernel(const uint64_t* __restrict__ ct,
+template <int LOGN, bool PM>
+__global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void modup_ntt_kernel(const uint64_t* __restrict__ ct,
                                                                       uint64_t* __restrict__ digits, uint64_t n,
                                                                       uint32_t L, uint32_t ginv,
                                                                       const Tw* __restrict__ tw_all,
                                                                       const LimbConst* __restrict__ ext) {
-  constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E, TOP = LOGN - LOGE;
+  constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E;
   __shared__ uint64_t lds[N + N / 16];
   const uint32_t L1 = L + 1;
   const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
@@ -264,14 +261,11 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void modup_ntt_kernel(const uint6
       x[k] = src >= (uint32_t)N && v ? ql - v : v;
     }
   }
-  if (m != l) {
+  if (!PM && m != l) {  // (PM: the transform takes any word below 2^60)
 #pragma unroll
     for (int k = 0; k < E; k++) x[k] = red_word(x[k], c);
   }
-  fwd_rest<LOGN, LOGE, 0>(x, lds, tid, tw_all + (size_t)m * N, c);
-#pragma unroll
-  for (int k = 0; k < E; k++) x[k] = fwd_canon(x[k], c);
-  exchange<LOGE, 0, TOP>(lds, x, tid);
+  ntt_fwd_regs<LOGN, LOGE, PM>(x, tw_all + (size_t)m * N, c, lds, tid);
   uint64_t* out = digits + (il * L1 + m) * N;
 #pragma unroll
   for (int k = 0; k < E; k++) out[tid + k * T] = x[k];
@@ -293,8 +287,8 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void modup_ntt_kernel(const uint6
 // batch may hold several chains of chain_cts ciphertexts that share the
 // input x but take different weights: ciphertext i uses x[i % chain_cts]
 // and the plaintext at wp + (i / chain_cts) * w_stride.
-template <int LOGN>
-__global__ __launch_bounds__((1 << LOGN) >> 3) void inner_intt_kernel(const uint64_t* __restrict__ digits,
+template <int LOGN, bool PM>
+__global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_kernel(const uint64_t* __restrict__ digits,
                                                                        const uint64_t* __restrict__ ksk,
                                                                        uint64_t* __restrict__ acc, uint64_t n,
                                                                        uint32_t L, uint32_t nd,
@@ -342,7 +336,7 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void inner_intt_kernel(const uint
   uint64_t x[E];
 #pragma unroll
   for (int k = 0; k < E; k++) x[k] = reduce128(hi[k], lo[k], c);
-  ntt_inv_regs<LOGN, LOGE>(x, tw_all + (size_t)m * N, c, lds, tid);
+  ntt_inv_regs<LOGN, LOGE, PM>(x, tw_all + (size_t)m * N, c, lds, tid);
   uint64_t* out = acc + ((i * 2 + comp) * L1 + m) * N;
 #pragma unroll
   for (int k = 0; k < E; k++) out[tid + k * T] = x[k];
@@ -428,35 +422,44 @@ hipError_t moddown_launch(const uint64_t* acc, const uint64_t* ct, uint64_t* out
   return hipGetLastError();
 }
 
+// One workgroup of N/8 threads per block of `grid`, in the transforms' form.
+#define HECONV_ROT(K, LN, ...)                                                                          \
+  do {                                                                                                  \
+    if (pm)                                                                                             \
+      hipLaunchKernelGGL((K<LN, true>), grid, dim3((1u << LN) / 8), 0, st, __VA_ARGS__);                \
+    else                                                                                                \
+      hipLaunchKernelGGL((K<LN, false>), grid, dim3((1u << LN) / 8), 0, st, __VA_ARGS__);               \
+  } while (0)
+
 bool ks_fwd_supported(uint32_t logN) { return logN >= 10 && logN <= 13; }
 
 hipError_t ks_fwd_launch(uint32_t logN, const uint64_t* ct, const uint64_t* ksk, uint64_t* acc, uint64_t n, uint32_t L,
-                         uint32_t ginv, const Tw* tw, const LimbConst* ext, hipStream_t st) {
+                         uint32_t ginv, const Tw* tw, const LimbConst* ext, bool pm, hipStream_t st) {
   const uint64_t blocks = (n + 7) / 8 * 8 * (L + 1);
   if (blocks > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;  // up to N/8 = 1024 threads
   if (!blocks) return hipSuccess;
   const dim3 grid((uint32_t)blocks);
   switch (logN) {
-    case 10: hipLaunchKernelGGL(ks_fwd_kernel<10>, grid, dim3(128), 0, st, ct, ksk, acc, n, L, ginv, tw, ext); break;
-    case 11: hipLaunchKernelGGL(ks_fwd_kernel<11>, grid, dim3(256), 0, st, ct, ksk, acc, n, L, ginv, tw, ext); break;
-    case 12: hipLaunchKernelGGL(ks_fwd_kernel<12>, grid, dim3(512), 0, st, ct, ksk, acc, n, L, ginv, tw, ext); break;
-    case 13: hipLaunchKernelGGL(ks_fwd_kernel<13>, grid, dim3(1024), 0, st, ct, ksk, acc, n, L, ginv, tw, ext); break;
+    case 10: HECONV_ROT(ks_fwd_kernel, 10, ct, ksk, acc, n, L, ginv, tw, ext); break;
+    case 11: HECONV_ROT(ks_fwd_kernel, 11, ct, ksk, acc, n, L, ginv, tw, ext); break;
+    case 12: HECONV_ROT(ks_fwd_kernel, 12, ct, ksk, acc, n, L, ginv, tw, ext); break;
+    case 13: HECONV_ROT(ks_fwd_kernel, 13, ct, ksk, acc, n, L, ginv, tw, ext); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits, uint64_t n, uint32_t L, uint32_t ginv,
-                            const Tw* tw, const LimbConst* ext, hipStream_t st) {
+                            const Tw* tw, const LimbConst* ext, bool pm, hipStream_t st) {
   const uint64_t blocks = (n * L + 7) / 8 * 8 * (L + 1);
   if (blocks > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;  // up to N/8 = 1024 threads
   if (!blocks) return hipSuccess;
   const dim3 grid((uint32_t)blocks);
   switch (logN) {
-    case 10: hipLaunchKernelGGL(modup_ntt_kernel<10>, grid, dim3(128), 0, st, ct, digits, n, L, ginv, tw, ext); break;
-    case 11: hipLaunchKernelGGL(modup_ntt_kernel<11>, grid, dim3(256), 0, st, ct, digits, n, L, ginv, tw, ext); break;
-    case 12: hipLaunchKernelGGL(modup_ntt_kernel<12>, grid, dim3(512), 0, st, ct, digits, n, L, ginv, tw, ext); break;
-    case 13: hipLaunchKernelGGL(modup_ntt_kernel<13>, grid, dim3(1024), 0, st, ct, digits, n, L, ginv, tw, ext); break;
+    case 10: HECONV_ROT(modup_ntt_kernel, 10, ct, digits, n, L, ginv, tw, ext); break;
+    case 11: HECONV_ROT(modup_ntt_kernel, 11, ct, digits, n, L, ginv, tw, ext); break;
+    case 12: HECONV_ROT(modup_ntt_kernel, 12, ct, digits, n, L, ginv, tw, ext); break;
+    case 13: HECONV_ROT(modup_ntt_kernel, 13, ct, digits, n, L, ginv, tw, ext); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -464,29 +467,17 @@ hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits,
 
 hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
                              uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
-                             uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, hipStream_t st) {
+                             uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, bool pm, hipStream_t st) {
   if (chain_cts == 0) chain_cts = n ? n : 1;
   const uint64_t blocks = (n * (L + 1) + 7) / 8 * 8 * 2;
   if (blocks > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;  // up to N/8 = 1024 threads
   if (!blocks) return hipSuccess;
   const dim3 grid((uint32_t)blocks);
   switch (logN) {
-    case 10:
-      hipLaunchKernelGGL(inner_intt_kernel<10>, grid, dim3(128), 0, st, digits, ksk, acc, n, L, nd, xp, wp, chain_cts,
-                         w_stride, tw_inv, ext);
-      break;
-    case 11:
-      hipLaunchKernelGGL(inner_intt_kernel<11>, grid, dim3(256), 0, st, digits, ksk, acc, n, L, nd, xp, wp, chain_cts,
-                         w_stride, tw_inv, ext);
-      break;
-    case 12:
-      hipLaunchKernelGGL(inner_intt_kernel<12>, grid, dim3(512), 0, st, digits, ksk, acc, n, L, nd, xp, wp, chain_cts,
-                         w_stride, tw_inv, ext);
-      break;
-    case 13:
-      hipLaunchKernelGGL(inner_intt_kernel<13>, grid, dim3(1024), 0, st, digits, ksk, acc, n, L, nd, xp, wp, chain_cts,
-                         w_stride, tw_inv, ext);
-      break;
+    case 10: HECONV_ROT(inner_intt_kernel, 10, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
+    case 11: HECONV_ROT(inner_intt_kernel, 11, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
+    case 12: HECONV_ROT(inner_intt_kernel, 12, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
+    case 13: HECONV_ROT(inner_intt_kernel, 13, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -499,5 +490,7 @@ hipError_t galois_key_launch(const uint64_t* work, uint64_t* ksk, uint32_t N, ui
   hipLaunchKernelGGL(galois_key_kernel, dim3(blocks), dim3(ROT_THREADS), 0, st, work, ksk, N, L, ext);
   return hipGetLastError();
 }
+
+#undef HECONV_ROT
 
 }  // namespace heconv
