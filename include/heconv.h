@@ -133,7 +133,9 @@ void he_ctx_destroy(he_ctx* ctx);
  * instead of one workgroup per polynomial, so that every compute unit
  * takes part; 0 = never.  Measured at N = 2^13: 10.2 against 14.2 us for 48
  * limb polynomials, 11.2 against 14.9 for 96, 14.5 against 15.3 for 144,
- * but 16.9 against 15.6 for 192.
+ * but 16.9 against 15.6 for 192.  (Contexts whose primes are all 2^b - delta
+ * with a small delta start with 0, or 80 at N = 2^14, for this field and
+ * ntt_inv_split_below: their one-grid transforms are faster.)
  * ntt_fp64: 1 = when every q_l < 2^50, every transform of the library
  * (except the batch executor's and the fused kernel's) runs in double
  * precision: residues are exact doubles and a modular product is two

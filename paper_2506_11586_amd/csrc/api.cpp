@@ -199,7 +199,14 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   }
   c->N = N, c->logN = log2u(N), c->L = L, c->t = prm->t;
   c->q.assign(prm->q, prm->q + L);
-  c->ntt_pm = true;
+  c->ntt_pm = std::all_of(c->q.begin(), c->q.end(), [](uint64_t v) { return pm_form(v).ok; });
+  // The signed one-grid transforms beat the two-grid ones (two launches, one
+  // more pass over the words) at every count up to N = 2^13: 48 limb
+  // polynomials at 2^13 8.8 us against 4.0 + 4.5 forward, 10.0 against 4.4 +
+  // 4.1 inverse, plus the second launch.  At 2^14 one workgroup fills a CU and
+  // takes 15-19 us: 48 limb polynomials 16.4 against 4.7 + 7.1 (19.1 against
+  // 5.6 + 6.4), 96 17.2 against 6.6 + 11.7 (19.9 against 8.5 + 10.6).
+  if (c->ntt_pm) c->tune.ntt_split_below = c->tune.ntt_inv_split_below = c->logN == 14 ? 80 : 0;
   const std::vector<uint64_t> dl = deltas(c->q, c->t);
   c->proto_ok = std::all_of(dl.begin(), dl.end(), [](uint64_t v) { return v != 0; });
   std::vector<Tw> fwd((size_t)L * N), inv((size_t)L * N);
@@ -213,7 +220,6 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     }
     c->psi.push_back(psi);
     const uint64_t psi_inv = mpow(psi, q - 2, q);
-    const bool pm = std::all_of(c->q.begin(), c->q.end(), [](uint64_t v) { return pm_form(v).ok; });
     for (int dir = 0; dir < 2; dir++) {
       const uint64_t base = dir ? psi_inv : psi;
       pw[0] = 1;
@@ -221,7 +227,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
       Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
       for (uint32_t k = 0; k < N; k++) {
         const uint64_t w = pw[bitrev(k, c->logN)];
-        tab[k] = Tw{w, pm ? 0 : shoup63(w, q)};
+        tab[k] = Tw{w, c->ntt_pm ? 0 : shoup63(w, q)};
       }
     }
     LimbConst k{};
@@ -244,7 +250,6 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
       k.pk = q << (63 - f.b);
       k.pninv = twp_of(k.ninv, q, f.b), k.pninv_w = twp_of(k.ninv_w, q, f.b);
     }
-    c->ntt_pm &= f.ok;
     c->lc.push_back(k);
   }
   c->all_pm = true;

@@ -38,8 +38,8 @@ __global__ __launch_bounds__((1 << LOGN) / FUSED_E, 4) void mac_intt_kernel(cons
   const uint32_t l = ml % L, m = ml / L;
   const uint32_t comp = r & 1, bs = r >> 1, b = bs / S, s = bs % S;
   const uint64_t LN = (uint64_t)L * N;
-  cgword* ip = in + ((((uint64_t)b * CB) * S + s) * 2 + comp) * LN + (uint64_t)l * N + tid;
-  cgword* wp = w + ((uint64_t)m * CB) * LN + (uint64_t)l * N + tid;
+  cgword* ip = in + ((((uint64_t)b * CB) * S + s) * 2 + comp) * LN + (uint64_t)l * N + io_base<4>(tid);
+  cgword* wp = w + ((uint64_t)m * CB) * LN + (uint64_t)l * N + io_base<4>(tid);
   const uint64_t in_cb = (uint64_t)S * 2 * LN;  // cb -> cb+1 in the input
   const LimbConst c = lcs[l];
 
@@ -61,8 +61,8 @@ __global__ __launch_bounds__((1 << LOGN) / FUSED_E, 4) void mac_intt_kernel(cons
         for (int d = 0; d < FUSED_DEPTH; d++)
 #pragma unroll
           for (int e = 0; e < G; e++) {
-            xv[d][e] = ip[(uint64_t)(cb + d) * in_cb + (g0 + e) * T];
-            wv[d][e] = wp[(uint64_t)(cb + d) * LN + (g0 + e) * T];
+            xv[d][e] = ip[(uint64_t)(cb + d) * in_cb + (g0 + e) * 64];
+            wv[d][e] = wp[(uint64_t)(cb + d) * LN + (g0 + e) * 64];
           }
 #pragma unroll
         for (int d = 0; d < FUSED_DEPTH; d++)
@@ -78,8 +78,8 @@ __global__ __launch_bounds__((1 << LOGN) / FUSED_E, 4) void mac_intt_kernel(cons
       for (; cb < cb1; cb++) {
 #pragma unroll
         for (int e = 0; e < G; e++) {
-          const Half30 xs = split30(ip[(uint64_t)cb * in_cb + (g0 + e) * T]);
-          const Half30 ws = split30(wp[(uint64_t)cb * LN + (g0 + e) * T]);
+          const Half30 xs = split30(ip[(uint64_t)cb * in_cb + (g0 + e) * 64]);
+          const Half30 ws = split30(wp[(uint64_t)cb * LN + (g0 + e) * 64]);
           a00[e] += (uint64_t)xs.lo * ws.lo;
           a01[e] += (uint64_t)xs.lo * ws.hi;
           a10[e] += (uint64_t)xs.hi * ws.lo;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__((1 << LOGN) / FUSED_E, 4) void mac_intt_kernel(cons
 #pragma unroll
     for (int e = 0; e < G; e++) x[g0 + e] = res[e];
   }
-  // x holds the NTT-form output in the top mapping (point tid + k*T)
+  // x holds the NTT-form output, point io_base + 64*k
   ntt_inv_regs<LOGN, 4, PM>(x, twi + (size_t)l * N, c, lds, tid);
   gword* op = out + ((((uint64_t)b * M + m) * S + s) * 2 + comp) * LN + (uint64_t)l * N + tid;
 #pragma unroll

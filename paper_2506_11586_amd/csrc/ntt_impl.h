@@ -23,11 +23,10 @@
 //
 // Thread/element mapping of a pass over bits [lo, lo+LOGE): register k of
 // thread t holds element j = (t mod 2^lo) | k << lo | (t >> lo) << (lo+LOGE).
-// The top pass (lo = n-LOGE) is j = t + k*N/E: global loads and stores use
-// it, so every wave access is a contiguous 512-byte run.  The forward
-// transform ends on lo = 0 and goes through LDS once more to store in the
-// top mapping; the inverse loads in the top mapping and goes through LDS to
-// start at lo = 0.  When n is not a multiple of LOGE the leftover bits are
+// The top pass (lo = n-LOGE) is j = t + k*N/E: coefficients are loaded and
+// stored in it, so every wave access is a contiguous 512-byte run.  NTT-form
+// words are loaded and stored in the mapping at lo = 6, whose runs are as
+// long and whose exchange with lo = 0 stays inside each wave (io_base).  When n is not a multiple of LOGE the leftover bits are
 // done by a partial pass at lo = 0.
 #pragma once
 #include "modarith.h"
@@ -217,8 +216,12 @@ __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], int tid, cons
 }
 
 // Move the thread's registers from the mapping at FROM to the mapping at TO
-// through LDS.  The leading barrier keeps the previous exchange's readers
-// ahead of this exchange's writers.
+// through LDS, element j at lds_pad(j).  A transform's exchanges form a
+// chain, so each thread writes the very entries that it read in the exchange
+// before (FROM is that one's TO): no other thread can still be reading them,
+// and one barrier, between the writes and the reads, orders a cross-wave
+// exchange.  A kernel that used LDS otherwise before its first exchange needs
+// a barrier there.
 //
 // Wave-local form.  In a mapping with LO <= 6 the 64 threads of wave w
 // (tid = 64w + i) hold exactly the elements whose index bits from 6+LOGE up
@@ -229,25 +232,33 @@ __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], int tid, cons
 // The LDS operations of one wave are performed in issue order, and the
 // empty asm statements with a memory clobber keep the compiler from moving
 // a read above a write (for one lane the addresses differ, so it otherwise
-// could).  The exchange before a wave-local one either is wave-local too or
-// ends with every wave reading its own block, so the leading barrier can go
-// as well.  A cross-wave exchange keeps both barriers, which also order it
-// after any wave-local one.
+// could).
 template <int LOGE, int FROM, int TO>
 __device__ __forceinline__ void exchange(uint64_t* lds, uint64_t (&x)[1 << LOGE], int tid) {
+  if constexpr (FROM == TO) return;
   constexpr bool WAVE = FROM <= 6 && TO <= 6;
+  // k << LO and the thread's part share no bit, so the padded index is their
+  // padded indexes' sum: one address and constant offsets
+  uint64_t* from = lds + lds_pad(elem_index<LOGE, FROM>(tid, 0));
+  const uint64_t* to = lds + lds_pad(elem_index<LOGE, TO>(tid, 0));
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int k = 0; k < (1 << LOGE); k++) from[lds_pad(k << FROM)] = x[k];
   if constexpr (WAVE)
     asm volatile("" ::: "memory");
   else
     __syncthreads();
 #pragma unroll
-  for (int k = 0; k < (1 << LOGE); k++) lds[lds_pad(elem_index<LOGE, FROM>(tid, k))] = x[k];
-  if constexpr (WAVE)
-    asm volatile("" ::: "memory");
-  else
-    __syncthreads();
-#pragma unroll
-  for (int k = 0; k < (1 << LOGE); k++) x[k] = lds[lds_pad(elem_index<LOGE, TO>(tid, k))];
+  for (int k = 0; k < (1 << LOGE); k++) x[k] = to[lds_pad(k << TO)];
+}
+
+// The mapping in which NTT-form words are loaded and stored, at LO = 6:
+// register k of lane i of wave w holds word i + 64*k of the wave's block of
+// 64*2^LOGE words.  Every access is a contiguous 512-byte run, as in the top
+// mapping, and the exchange with bit 0 is wave-local.
+template <int LOGE>
+__device__ __forceinline__ int io_base(int tid) {
+  return elem_index<LOGE, 6>(tid, 0);
 }
 
 // Forward full passes at LO = LOGN-LOGE*(P+1), then the partial pass.
@@ -283,18 +294,18 @@ __device__ __forceinline__ void inv_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds
 
 // Forward transform of values in registers in the top mapping (register k of
 // thread t = entry t + k*N/E; canonical, PM: any below 2^60), left canonical
-// in the same mapping.
+// in the mapping of NTT-form words (register k = entry io_base + 64*k).
 template <int LOGN, int LOGE, bool PM>
 __device__ __forceinline__ void ntt_fwd_regs(uint64_t (&x)[1 << LOGE], const Tw* __restrict__ tw, const LimbConst& c,
                                              uint64_t* lds, int tid) {
-  constexpr int E = 1 << LOGE, TOP = LOGN - LOGE;
+  constexpr int E = 1 << LOGE;
   const PmRegs pk = pm_regs(c);
 #pragma unroll
   for (int k = 0; k < E; k++) x[k] = fwd_in<PM>(x[k]);
   fwd_rest<LOGN, LOGE, 0, PM>(x, lds, tid, tw, c, pk);
 #pragma unroll
   for (int k = 0; k < E; k++) x[k] = fwd_canon<PM>(x[k], c);
-  exchange<LOGE, 0, TOP>(lds, x, tid);
+  exchange<LOGE, 0, 6>(lds, x, tid);
 }
 
 // Forward transform of one limb polynomial a[N] (in place) by the calling
@@ -306,20 +317,21 @@ __device__ __forceinline__ void ntt_fwd_poly(gword* __restrict__ a, const Tw* __
   uint64_t x[E];
 #pragma unroll
   for (int k = 0; k < E; k++) x[k] = a[tid + k * T];
-  ntt_fwd_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);  // back to j = tid + k*T for a coalesced store
+  ntt_fwd_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);
+  a += io_base<LOGE>(tid);
 #pragma unroll
-  for (int k = 0; k < E; k++) a[tid + k * T] = x[k];
+  for (int k = 0; k < E; k++) a[64 * k] = x[k];
 }
 
-// Inverse transform of NTT values already in registers in the top mapping
-// (register k of thread t = entry t + k*N/E); leaves the coefficients, in
-// the same mapping, canonical.
+// Inverse transform of NTT values already in registers in the mapping of
+// NTT-form words (register k = entry io_base + 64*k); leaves the
+// coefficients canonical in the top mapping (entry t + k*N/E).
 template <int LOGN, int LOGE, bool PM>
 __device__ __forceinline__ void ntt_inv_regs(uint64_t (&x)[1 << LOGE], const Tw* __restrict__ tw, const LimbConst& c,
                                              uint64_t* lds, int tid) {
-  constexpr int TOP = LOGN - LOGE, REM = LOGN % LOGE;
+  constexpr int REM = LOGN % LOGE;
   const PmRegs pk = pm_regs(c);
-  exchange<LOGE, TOP, 0>(lds, x, tid);
+  exchange<LOGE, 6, 0>(lds, x, tid);
   if constexpr (REM > 0) inv_pass<LOGN, LOGE, 0, LOGE - REM, false, PM>(x, tid, tw, c, pk);
   inv_rest<LOGN, LOGE, 0, PM>(x, lds, tid, tw, c, pk);
 }
@@ -334,11 +346,11 @@ __device__ __forceinline__ void ntt_inv_poly(gword* __restrict__ a, const Tw* __
   constexpr int N = 1 << LOGN, E = 1 << LOGE, T = N / E;
   uint64_t x[E];
 #pragma unroll
-  for (int k = 0; k < E; k++) {  // coalesced, top mapping
+  for (int k = 0; k < E; k++) {
     if constexpr (NT)
-      x[k] = __builtin_nontemporal_load(&a[tid + k * T]);
+      x[k] = __builtin_nontemporal_load(&a[io_base<LOGE>(tid) + 64 * k]);
     else
-      x[k] = a[tid + k * T];
+      x[k] = a[io_base<LOGE>(tid) + 64 * k];
   }
   ntt_inv_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);
 #pragma unroll

@@ -104,9 +104,10 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_fwd_split_b(uint64_t* __restrict_
   split_b_rest<LOGN, 0, PM>(x, lds, tid, tw, c, pk, jb);
 #pragma unroll
   for (int k = 0; k < 8; k++) x[k] = fwd_canon<PM>(x[k], c);
-  exchange<3, 0, 7>(lds, x, tid);  // to local index tid + 128k for a coalesced store
+  exchange<3, 0, 6>(lds, x, tid);
+  a += io_base<3>(tid);
 #pragma unroll
-  for (int k = 0; k < 8; k++) a[tid + 128 * k] = x[k];
+  for (int k = 0; k < 8; k++) a[64 * k] = x[k];
 }
 
 // Inverse in two grids, the mirror image: grid C takes 1024 consecutive
@@ -148,8 +149,8 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_inv_split_c(uint64_t* __restrict_
   const PmRegs pk = pm_regs(c);
   uint64_t x[8];
 #pragma unroll
-  for (int k = 0; k < 8; k++) x[k] = a[tid + 128 * k];  // local index tid + 128k: the mapping at 7
-  exchange<3, 7, 0>(lds, x, tid);
+  for (int k = 0; k < 8; k++) x[k] = a[io_base<3>(tid) + 64 * k];
+  exchange<3, 6, 0>(lds, x, tid);
   if constexpr (REM > 0) inv_pass<LOGN, 3, 0, 3 - REM, false, PM>(x, tid, tw, c, pk, jb);
   inv_split_c_rest<LOGN, 0, PM>(x, lds, tid, tw, c, pk, jb);
 #pragma unroll

@@ -35,9 +35,14 @@ inline TwP twp_of(uint64_t w, uint64_t q, uint32_t b) {
     hi = (int32_t)((v + (1ll << 27)) >> 28);
     lo = (int32_t)(v - ((int64_t)hi << 28));
   };
+  // w * 2^32 = hi * 2^b + lo with hi < 2^32: hi * delta + lo is below 2^56 + 2^b, brought below 2q by one more fold
+  const uint64_t delta = (1ull << b) - q;
+  uint64_t v = (w >> (b - 32)) * delta + ((w & ((1ull << (b - 32)) - 1)) << 32);
+  v = (v >> b) * delta + (v & ((1ull << b) - 1));
+  if (v >= q) v -= q;
   TwP t;
   split(w, t.w0, t.w1);
-  split((uint64_t)(((unsigned __int128)w << 32) % q), t.v0, t.v1);
+  split(v, t.v0, t.v1);
   return t;
 }
 

@@ -176,12 +176,12 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void ks_fwd_kernel(const uint64_t
     const Tw* tw = tw_all + __builtin_amdgcn_readfirstlane(off);
     const uint64_t* row = ct + (i * 2 * L + l) * N;
     uint64_t x[E];
+    __syncthreads();  // the previous digit's last LDS reads are done
     if (ginv == 1) {
 #pragma unroll
       for (int k = 0; k < E; k++) x[k] = row[tid + k * T];
     } else {
       const uint64_t ql = ext[l].q;
-      __syncthreads();  // the previous digit's last LDS reads are done
 #pragma unroll
       for (int k = 0; k < E; k++) lds[lds_pad(tid + k * T)] = row[tid + k * T];
       __syncthreads();
@@ -191,34 +191,35 @@ __global__ __launch_bounds__((1 << LOGN) >> 3) void ks_fwd_kernel(const uint64_t
         const uint64_t v = lds[lds_pad(src & (N - 1))];
         x[k] = src >= (uint32_t)N && v ? ql - v : v;
       }
+      __syncthreads();  // the row is read before the transform reuses its LDS
     }
     if (!PM && m != l) {  // (PM: the transform takes any word below 2^60)
 #pragma unroll
       for (int k = 0; k < E; k++) x[k] = red_word(x[k], c);
     }
-    ntt_fwd_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);  // entry tid + k*T, as the key rows are read
+    ntt_fwd_regs<LOGN, LOGE, PM>(x, tw, c, lds, tid);  // entry io_base + 64*k, as the key rows are read
     // the key loads are addressed from a value defined here, so they are
     // issued after the transform rather than held in registers through it
-    int tk = tid;
+    int tk = io_base<LOGE>(tid);
     asm volatile("" : "+v"(tk));
     const uint64_t* ka = ksk + ((uint64_t)(l * 2) * L1 + m) * N;
     const uint64_t* kb = ka + (uint64_t)L1 * N;
 #pragma unroll
     for (int k = 0; k < E; k++) {
       uint64_t hi, lo;
-      mul_wide(x[k], ka[tk + k * T], hi, lo);
+      mul_wide(x[k], ka[tk + 64 * k], hi, lo);
       sa[k] = csub(sa[k] + reduce128(hi, lo, c), c.q);
-      mul_wide(x[k], kb[tk + k * T], hi, lo);
+      mul_wide(x[k], kb[tk + 64 * k], hi, lo);
       sb[k] = csub(sb[k] + reduce128(hi, lo, c), c.q);
     }
   }
-  const int tid = threadIdx.x;
+  const int io = io_base<LOGE>(threadIdx.x);
   uint64_t* oa = acc + ((i * 2) * L1 + m) * N;
   uint64_t* ob = oa + (uint64_t)L1 * N;
 #pragma unroll
   for (int k = 0; k < E; k++) {
-    oa[tid + k * T] = sa[k];
-    ob[tid + k * T] = sb[k];
+    oa[io + 64 * k] = sa[k];
+    ob[io + 64 * k] = sb[k];
   }
 }
 
@@ -260,15 +261,16 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void modup_ntt_kern
       const uint64_t v = lds[lds_pad(src & (N - 1))];
       x[k] = src >= (uint32_t)N && v ? ql - v : v;
     }
+    __syncthreads();  // the row is read before the transform reuses its LDS
   }
   if (!PM && m != l) {  // (PM: the transform takes any word below 2^60)
 #pragma unroll
     for (int k = 0; k < E; k++) x[k] = red_word(x[k], c);
   }
   ntt_fwd_regs<LOGN, LOGE, PM>(x, tw_all + (size_t)m * N, c, lds, tid);
-  uint64_t* out = digits + (il * L1 + m) * N;
+  uint64_t* out = digits + (il * L1 + m) * N + io_base<LOGE>(tid);
 #pragma unroll
-  for (int k = 0; k < E; k++) out[tid + k * T] = x[k];
+  for (int k = 0; k < E; k++) out[64 * k] = x[k];
 }
 
 // Inner product fused into the inverse transform: one workgroup per
@@ -314,10 +316,10 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_ker
   // L <= 7 digit products and one plaintext product, each below 2^120: the
   // 128-bit sums do not overflow.  Rows are read through buffer resources
   // (the row base in scalar registers, the lane's byte offset fixed, the
-  // register's offset k*T*8 a scalar), so a load costs no per-lane address
+  // register's offset 64*k*8 a scalar), so a load costs no per-lane address
   // arithmetic.
   const bool plain = xp && m < L;
-  const uint32_t lane = (uint32_t)tid * 8;
+  const uint32_t lane = (uint32_t)io_base<LOGE>(tid) * 8;
   for (uint32_t l = 0; l < nd + (plain ? 1 : 0); l++) {
     const uint64_t* d =
         l < nd ? digits + ((i * L + l) * L1 + m) * N : xp + (((i % chain_cts) * 2 + comp) * L + m) * N;
@@ -328,7 +330,7 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_ker
 #pragma unroll
     for (int k = 0; k < E; k++) {
       uint64_t ph, pl;
-      mul_wide(mac_load(rd, lane, (uint32_t)(k * T * 8)), mac_load(rk, lane, (uint32_t)(k * T * 8)), ph, pl);
+      mul_wide(mac_load(rd, lane, (uint32_t)(64 * k * 8)), mac_load(rk, lane, (uint32_t)(64 * k * 8)), ph, pl);
       lo[k] += pl;
       hi[k] += ph + (lo[k] < pl);
     }
