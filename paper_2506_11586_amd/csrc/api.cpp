@@ -12,6 +12,7 @@
 #include "heconv.h"
 #include "ctx.h"
 #include "pm_form.h"
+#include "tw_layout.h"
 #include "kernels.h"
 
 using heconv::LimbConst;
@@ -70,6 +71,19 @@ unsigned bitrev(unsigned x, unsigned bits) {
   return r;
 }
 
+// Products by one factor w < q < 2^62 without a division each: x*w mod q for
+// x < q by the factor's Shoup quotient.  (The root search and the tables are
+// chains of 3N products a limb; a 128-bit remainder each took most of
+// he_ctx_create's time.)
+struct MulBy {
+  uint64_t w, wsh, q;
+  MulBy(uint64_t w_, uint64_t q_) : w(w_), wsh((uint64_t)(((u128)w_ << 64) / q_)), q(q_) {}
+  uint64_t operator()(uint64_t x) const {
+    const uint64_t r = x * w - (uint64_t)(((u128)x * wsh) >> 64) * q;
+    return r >= q ? r - q : r;
+  }
+};
+
 // The smallest primitive 2N-th root of unity mod q (q = 1 mod 2N).  A
 // primitive 2N-th root r is c^((q-1)/2N) for some c with r^N = -1; every
 // other is an odd power of r.
@@ -80,9 +94,9 @@ uint64_t min_root(uint64_t q, uint32_t N) {
     if (mpow(cand, N, q) == q - 1) r = cand;
   }
   if (!r) return 0;
-  const uint64_t r2 = mmul(r, r, q);
+  const MulBy r2(mmul(r, r, q), q);
   uint64_t best = r;
-  for (uint64_t k = 1, v = r; k < 2ull * N; k += 2, v = mmul(v, r2, q))
+  for (uint64_t k = 1, v = r; k < 2ull * N; k += 2, v = r2(v))
     if (v < best) best = v;
   return best;
 }
@@ -223,7 +237,8 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     for (int dir = 0; dir < 2; dir++) {
       const uint64_t base = dir ? psi_inv : psi;
       pw[0] = 1;
-      for (uint32_t i = 1; i < N; i++) pw[i] = mmul(pw[i - 1], base, q);
+      const MulBy by(base, q);
+      for (uint32_t i = 1; i < N; i++) pw[i] = by(pw[i - 1]);
       Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
       for (uint32_t k = 0; k < N; k++) {
         const uint64_t w = pw[bitrev(k, c->logN)];
@@ -286,14 +301,21 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
       heconv::f64_const_fill(fc.data() + heconv::f64_const_size() * l, (double)c->q[l], 1.0 / (double)c->q[l],
                              (double)c->lc[l].ninv, (double)c->lc[l].ninv_w);
   }
-  if (c->ntt_pm)  // the tables of the signed transforms
-    for (uint32_t l = 0; l < L; l++) {
-      const uint32_t b = c->lc[l].pb32 + 32;
-      for (size_t i = (size_t)l * N; i < (size_t)(l + 1) * N; i++)
-        for (Tw* tab : {fwd.data(), inv.data()}) {
-          const TwP p = twp_of(tab[i].w, c->q[l], b);
-          std::memcpy(&tab[i], &p, sizeof(Tw));
+  // into the transforms' order of entries, and with ntt_pm the signed factors
+  std::vector<Tw> ord(N);
+  for (uint32_t l = 0; l < L; l++)
+    for (Tw* tab : {fwd.data() + (size_t)l * N, inv.data() + (size_t)l * N}) {
+      ord[0] = tab[0];
+      for (uint32_t st = 0; st < c->logN; st++) {
+        for (uint32_t i = 0; i < (1u << st); i++) {
+          Tw& to = ord[heconv::tw_place((int)c->logN, (int)st, i)];
+          to = tab[(1u << st) + i];
+          if (!c->ntt_pm) continue;
+          const TwP p = twp_of(to.w, c->q[l], c->lc[l].pb32 + 32);
+          std::memcpy(&to, &p, sizeof(Tw));
         }
+      }
+      std::memcpy(tab, ord.data(), sizeof(Tw) * N);
     }
   const size_t tb = sizeof(Tw) * (size_t)L * N;
   if (hipMalloc(&c->d_fwd, tb) != hipSuccess || hipMalloc(&c->d_inv, tb) != hipSuccess ||

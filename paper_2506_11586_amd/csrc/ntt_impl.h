@@ -29,7 +29,10 @@
 // long and whose exchange with lo = 0 stays inside each wave (io_base).  When n is not a multiple of LOGE the leftover bits are
 // done by a partial pass at lo = 0.
 #pragma once
+#include <type_traits>
+
 #include "modarith.h"
+#include "tw_layout.h"
 
 
 namespace heconv {
@@ -65,6 +68,38 @@ __device__ __forceinline__ uint64_t fwd_canon(uint64_t x, const LimbConst& c) {
   return canon_below6q(x, c.neg3q, c.neg2q, c.negq);
 }
 
+// The twiddles of a pass's stages [U0, LOGE) in the order the stages use them
+// (stage u holds 2^u of them from slot 2^u - 1 on; the inverse runs the stages
+// backwards over the same slots), at their places in the table (tw_layout.h).
+// They are loaded before the exchange that precedes the pass, so that their
+// latency passes behind it.  24576 limb polynomials with both against loads at
+// the stage and g fastest throughout: N = 16384 forward 1960 -> 1770 us,
+// inverse 2200 -> 1840; N = 8192 835 -> 830 and 887 -> 845 (a bench-wide 3.8
+// TB/s, where a copy in place without the arithmetic runs 5.5).  jb: index of
+// the workgroup's first element when it transforms a block of a longer
+// polynomial (the stages on bits below the block size only; jb a multiple of
+// the block size), else 0.
+// TLOGN: log2 of the length whose table tw is (of the longer polynomial's,
+// whose first stages a shorter transform's coincide with).
+template <int LOGN, int LOGE, int LO, int U0, bool PM, int TLOGN = LOGN>
+struct PassTw {
+  using T = std::conditional_t<PM, TwP, Tw>;
+  T t[(1 << LOGE) - 1];
+  __device__ __forceinline__ void load(int tid, const Tw* __restrict__ tw, uint32_t jb = 0) {
+    const uint32_t high = (uint32_t)block_of<LO>(tid) + (jb >> (LO + LOGE));
+#pragma unroll
+    for (int u = U0; u < LOGE; u++) {
+      const int s = LOGN - LOGE - LO + u;  // stage index
+#pragma unroll
+      for (int g = 0; g < (1 << u); g++) {
+        const uint32_t at =
+            tw_u(TLOGN, s) == u && u ? tw_place_hg(s, u, high, g) : tw_place(TLOGN, s, (high << u) + g);
+        t[(1 << u) - 1 + g] = reinterpret_cast<const T*>(tw)[at];
+      }
+    }
+  }
+};
+
 // Forward values of the PM form are stored with a bias of 2^31 (pm_mul_biased);
 // the bias passes through X + T and X - T unchanged.  A loaded word gets it
 // here, and fwd_canon takes it off.
@@ -82,17 +117,14 @@ __device__ __forceinline__ uint64_t fwd_canon(uint64_t x, const LimbConst& c) {
     return canon_below6q(x, c.neg3q, c.neg2q, c.negq);
 }
 
-// Forward stages u in [U0, LOGE) of the pass at bit offset LO.  jb: index
-// of the workgroup's first element when it transforms a block of a longer
-// polynomial (the stages on bits below the block size only; jb a multiple of
-// the block size), else 0.
+// Forward stages u in [U0, LOGE) of the pass at bit offset LO: butterflies on
+// bit LO+LOGE-1-u.
 // PM: a stage takes a bound of a to a + T(a), so canonical inputs (1u) reach
 // 7.2u after seven stages, and values brought to 0.5u 7.54u after eight; RED
 // brings them there before the pass (fwd_red).
-template <int LOGN, int LOGE, int LO, int U0, bool PM, bool RED = false>
-__device__ __forceinline__ void fwd_pass(uint64_t (&x)[1 << LOGE], int tid, const Tw* __restrict__ tw,
-                                         const LimbConst& c, const PmRegs& pk, uint32_t jb = 0) {
-  const int high = block_of<LO>(tid);
+template <bool RED, int LOGN, int LOGE, int LO, int U0, bool PM, int TLOGN>
+__device__ __forceinline__ void fwd_pass(uint64_t (&x)[1 << LOGE], const PassTw<LOGN, LOGE, LO, U0, PM, TLOGN>& tw,
+                                         const LimbConst& c, const PmRegs& pk) {
   const uint64_t q3 = c.three_q;
   if constexpr (PM && RED) {
 #pragma unroll
@@ -100,25 +132,18 @@ __device__ __forceinline__ void fwd_pass(uint64_t (&x)[1 << LOGE], int tid, cons
   }
 #pragma unroll
   for (int u = U0; u < LOGE; u++) {
-    const int s = LOGN - LOGE - LO + u;  // stage index: butterflies on bit LO+LOGE-1-u
     const int half = 1 << (LOGE - 1 - u);
 #pragma unroll
     for (int g = 0; g < (1 << u); g++) {
-      const uint32_t ti = (1 << s) + (jb >> (LO + LOGE - u)) + (high << u) + g;
-      if constexpr (PM) {
-        const TwP t = reinterpret_cast<const TwP*>(tw)[ti];
+      const auto t = tw.t[(1 << u) - 1 + g];
 #pragma unroll
-        for (int e = 0; e < half; e++) {
-          const int k0 = g * 2 * half + e, k1 = k0 + half;
+      for (int e = 0; e < half; e++) {
+        const int k0 = g * 2 * half + e, k1 = k0 + half;
+        if constexpr (PM) {
           const uint64_t X = x[k0], T = pm_mul_biased(x[k1], t, pk);
           x[k0] = X + T;
           x[k1] = X - T;
-        }
-      } else {
-        const Tw t = tw[ti];
-#pragma unroll
-        for (int e = 0; e < half; e++) {
-          const int k0 = g * 2 * half + e, k1 = k0 + half;
+        } else {
           const uint64_t X = csub_neg(x[k0], c.neg3q);
           const uint64_t T = mul_shoup_2q(x[k1], t.w, t.wsh, c.neg2q);
           x[k0] = X + T;
@@ -144,8 +169,7 @@ constexpr int fwd_since(int P) {
 
 // Inverse stages u from LOGE-1 down to U0 of the pass at LO.  With LAST, the
 // stage on the top bit (u = 0 of the pass at n-LOGE) also applies N^-1 and
-// leaves canonical values.  jb as in fwd_pass (a block's first element, for
-// the stages on bits below the block size; never with LAST).
+// leaves canonical values.
 //
 // PM: with s and p for the sum and the product of a stage, an input bound a
 // <= 1.8u gives after two stages ss 4a = 7.2u, sp T(4a) = 1.0u, ps 2T(2a) =
@@ -156,14 +180,12 @@ constexpr int fwd_since(int P) {
 // canonical inputs brings its sums (2u) to 0.5u.  So every pass starts below
 // 1.8u again, and no value reaches 7.5u.  Register k's bit j is 0 where
 // stage j of the pass left it a sum.
-template <int LOGN, int LOGE, int LO, int U0, bool LAST, bool PM>
-__device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], int tid, const Tw* __restrict__ tw,
-                                         const LimbConst& c, const PmRegs& pk, uint32_t jb = 0) {
-  const int high = block_of<LO>(tid);
+template <bool LAST, int LOGN, int LOGE, int LO, int U0, bool PM, int TLOGN>
+__device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], const PassTw<LOGN, LOGE, LO, U0, PM, TLOGN>& tw,
+                                         const LimbConst& c, const PmRegs& pk) {
   const uint64_t q3 = c.three_q;
 #pragma unroll
   for (int u = LOGE - 1; u >= U0; u--) {
-    const int s = LOGN - LOGE - LO + u;
     const int half = 1 << (LOGE - 1 - u);
     if (LAST && u == 0) {
 #pragma unroll
@@ -182,22 +204,15 @@ __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], int tid, cons
     }
 #pragma unroll
     for (int g = 0; g < (1 << u); g++) {
-      const uint32_t ti = (1 << s) + (jb >> (LO + LOGE - u)) + (high << u) + g;
-      if constexpr (PM) {
-        const TwP t = reinterpret_cast<const TwP*>(tw)[ti];
+      const auto t = tw.t[(1 << u) - 1 + g];
 #pragma unroll
-        for (int e = 0; e < half; e++) {
-          const int k0 = g * 2 * half + e, k1 = k0 + half;
-          const uint64_t X = x[k0], Y = x[k1];
+      for (int e = 0; e < half; e++) {
+        const int k0 = g * 2 * half + e, k1 = k0 + half;
+        const uint64_t X = x[k0], Y = x[k1];
+        if constexpr (PM) {
           x[k0] = X + Y;
           x[k1] = pm_mul_val(X - Y, t, pk);
-        }
-      } else {
-        const Tw t = tw[ti];
-#pragma unroll
-        for (int e = 0; e < half; e++) {
-          const int k0 = g * 2 * half + e, k1 = k0 + half;
-          uint64_t X = x[k0], Y = x[k1];
+        } else {
           x[k0] = csub_neg(X + Y, c.neg3q);
           x[k1] = mul_shoup_2q(X - Y + q3, t.w, t.wsh, c.neg2q);
         }
@@ -266,29 +281,29 @@ template <int LOGN, int LOGE, int P, bool PM>
 __device__ __forceinline__ void fwd_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds, int tid,
                                          const Tw* __restrict__ tw, const LimbConst& c, const PmRegs& pk) {
   constexpr int NFULL = LOGN / LOGE, REM = LOGN % LOGE;
-  if constexpr (P < NFULL) {
-    constexpr int LO = LOGN - LOGE * (P + 1);
-    if constexpr (P > 0) exchange<LOGE, LO + LOGE, LO>(lds, x, tid);
-    fwd_pass<LOGN, LOGE, LO, 0, PM, (fwd_since<LOGE>(P) + LOGE > 7)>(x, tid, tw, c, pk);
+  if constexpr (P < NFULL || (P == NFULL && REM > 0)) {
+    constexpr int LO = P < NFULL ? LOGN - LOGE * (P + 1) : 0, U0 = P < NFULL ? 0 : LOGE - REM;
+    PassTw<LOGN, LOGE, LO, U0, PM> t;
+    t.load(tid, tw);
+    if constexpr (P > 0) exchange<LOGE, LOGN - LOGE * P, LO>(lds, x, tid);
+    fwd_pass<(fwd_since<LOGE>(P) + LOGE - U0 > 7)>(x, t, c, pk);
     fwd_rest<LOGN, LOGE, P + 1, PM>(x, lds, tid, tw, c, pk);
-  } else if constexpr (REM > 0) {
-    exchange<LOGE, LOGN - LOGE * NFULL, 0>(lds, x, tid);
-    fwd_pass<LOGN, LOGE, 0, LOGE - REM, PM, (fwd_since<LOGE>(NFULL) + REM > 7)>(x, tid, tw, c, pk);
   }
 }
 
-// Inverse full passes at LO = REM + LOGE*P (the partial pass at LO = 0, if
-// any, has already run).
-template <int LOGN, int LOGE, int P, bool PM>
+// Inverse passes: the partial one at LO = 0 (P = -1, if any), then full ones
+// at LO = REM + LOGE*P, each after the exchange from the mapping at PREV.
+template <int LOGN, int LOGE, int P, int PREV, bool PM>
 __device__ __forceinline__ void inv_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds, int tid,
                                          const Tw* __restrict__ tw, const LimbConst& c, const PmRegs& pk) {
   constexpr int NFULL = LOGN / LOGE, REM = LOGN % LOGE;
   if constexpr (P < NFULL) {
-    constexpr int LO = REM + LOGE * P;
-    constexpr int PREV = (P == 0) ? 0 : REM + LOGE * (P - 1);
-    if constexpr (P > 0 || REM > 0) exchange<LOGE, PREV, LO>(lds, x, tid);
-    inv_pass<LOGN, LOGE, LO, 0, (P == NFULL - 1), PM>(x, tid, tw, c, pk);
-    inv_rest<LOGN, LOGE, P + 1, PM>(x, lds, tid, tw, c, pk);
+    constexpr int LO = P < 0 ? 0 : REM + LOGE * P, U0 = P < 0 ? LOGE - REM : 0;
+    PassTw<LOGN, LOGE, LO, U0, PM> t;
+    t.load(tid, tw);
+    exchange<LOGE, PREV, LO>(lds, x, tid);
+    inv_pass<(P == NFULL - 1)>(x, t, c, pk);
+    inv_rest<LOGN, LOGE, P + 1, LO, PM>(x, lds, tid, tw, c, pk);
   }
 }
 
@@ -331,9 +346,7 @@ __device__ __forceinline__ void ntt_inv_regs(uint64_t (&x)[1 << LOGE], const Tw*
                                              uint64_t* lds, int tid) {
   constexpr int REM = LOGN % LOGE;
   const PmRegs pk = pm_regs(c);
-  exchange<LOGE, 6, 0>(lds, x, tid);
-  if constexpr (REM > 0) inv_pass<LOGN, LOGE, 0, LOGE - REM, false, PM>(x, tid, tw, c, pk);
-  inv_rest<LOGN, LOGE, 0, PM>(x, lds, tid, tw, c, pk);
+  inv_rest<LOGN, LOGE, (REM > 0 ? -1 : 0), 6, PM>(x, lds, tid, tw, c, pk);
 }
 
 // Inverse transform of one limb polynomial a[N] (in place).  With NT the

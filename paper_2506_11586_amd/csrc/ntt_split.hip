@@ -56,9 +56,13 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_fwd_split_a(uint64_t* __restrict_
     const int v = tid + 128 * k;
     x[k] = fwd_in<PM>(a[(v & 15) + (size_t)G * (v >> 4)]);
   }
-  fwd_pass<10, 3, 7, 0, PM>(x, tid, tw, c, pk);
+  PassTw<10, 3, 7, 0, PM, LOGN> t0;
+  t0.load(tid, tw);
+  fwd_pass<false>(x, t0, c, pk);
+  PassTw<10, 3, 4, 0, PM, LOGN> t1;
+  t1.load(tid, tw);
   exchange<3, 7, 4>(lds, x, tid);
-  fwd_pass<10, 3, 4, 0, PM>(x, tid, tw, c, pk);
+  fwd_pass<false>(x, t1, c, pk);
 #pragma unroll
   for (int k = 0; k < 8; k++) {
     const int v = elem_index<3, 4>(tid, k);
@@ -72,14 +76,13 @@ __device__ __forceinline__ void split_b_rest(uint64_t (&x)[8], uint64_t* lds, in
                                              const LimbConst& c, const PmRegs& pk, uint32_t jb) {
   constexpr int NB = LOGN - 6;  // stages in this grid
   constexpr int NFULL = NB / 3, REM = NB % 3;
-  if constexpr (P < NFULL) {
-    constexpr int LO = NB - 3 * (P + 1);
-    if constexpr (P > 0) exchange<3, LO + 3, LO>(lds, x, tid);
-    fwd_pass<LOGN, 3, LO, 0, PM, P == 0>(x, tid, tw, c, pk, jb);
+  if constexpr (P < NFULL || (P == NFULL && REM > 0)) {
+    constexpr int LO = P < NFULL ? NB - 3 * (P + 1) : 0, U0 = P < NFULL ? 0 : 3 - REM;
+    PassTw<LOGN, 3, LO, U0, PM> t;
+    t.load(tid, tw, jb);
+    if constexpr (P > 0) exchange<3, NB - 3 * P, LO>(lds, x, tid);
+    fwd_pass<(P == 0)>(x, t, c, pk);
     split_b_rest<LOGN, P + 1, PM>(x, lds, tid, tw, c, pk, jb);
-  } else if constexpr (REM > 0) {
-    exchange<3, NB - 3 * NFULL, 0>(lds, x, tid);
-    fwd_pass<LOGN, 3, 0, 3 - REM, PM>(x, tid, tw, c, pk, jb);
   }
 }
 
@@ -117,17 +120,18 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_fwd_split_b(uint64_t* __restrict_
 // inverse in the index v = i*16 + (g - g0), the top one applying N^-1.
 // Values keep the transform's lazy form between the grids (below 3q; PM:
 // signed, below 1.8 * 2^60); the result is canonical.
-template <int LOGN, int P, bool PM>
+template <int LOGN, int P, int PREV, bool PM>
 __device__ __forceinline__ void inv_split_c_rest(uint64_t (&x)[8], uint64_t* lds, int tid,
                                                  const Tw* __restrict__ tw, const LimbConst& c,
                                                  const PmRegs& pk, uint32_t jb) {
   constexpr int NB = LOGN - 6, NFULL = NB / 3, REM = NB % 3;
   if constexpr (P < NFULL) {
-    constexpr int LO = REM + 3 * P;
-    constexpr int PREV = (P == 0) ? 0 : REM + 3 * (P - 1);
-    if constexpr (P > 0 || REM > 0) exchange<3, PREV, LO>(lds, x, tid);
-    inv_pass<LOGN, 3, LO, 0, false, PM>(x, tid, tw, c, pk, jb);
-    inv_split_c_rest<LOGN, P + 1, PM>(x, lds, tid, tw, c, pk, jb);
+    constexpr int LO = P < 0 ? 0 : REM + 3 * P, U0 = P < 0 ? 3 - REM : 0;
+    PassTw<LOGN, 3, LO, U0, PM> t;
+    t.load(tid, tw, jb);
+    exchange<3, PREV, LO>(lds, x, tid);
+    inv_pass<false>(x, t, c, pk);
+    inv_split_c_rest<LOGN, P + 1, LO, PM>(x, lds, tid, tw, c, pk, jb);
   }
 }
 
@@ -150,9 +154,7 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_inv_split_c(uint64_t* __restrict_
   uint64_t x[8];
 #pragma unroll
   for (int k = 0; k < 8; k++) x[k] = a[io_base<3>(tid) + 64 * k];
-  exchange<3, 6, 0>(lds, x, tid);
-  if constexpr (REM > 0) inv_pass<LOGN, 3, 0, 3 - REM, false, PM>(x, tid, tw, c, pk, jb);
-  inv_split_c_rest<LOGN, 0, PM>(x, lds, tid, tw, c, pk, jb);
+  inv_split_c_rest<LOGN, (REM > 0 ? -1 : 0), 6, PM>(x, lds, tid, tw, c, pk, jb);
 #pragma unroll
   for (int k = 0; k < 8; k++) a[elem_index<3, LAST_LO>(tid, k)] = x[k];
 }
@@ -178,9 +180,13 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_inv_split_d(uint64_t* __restrict_
     const int v = elem_index<3, 4>(tid, k);
     x[k] = a[(v & 15) + (size_t)G * (v >> 4)];
   }
-  inv_pass<10, 3, 4, 0, false, PM>(x, tid, tw, c, pk);
+  PassTw<10, 3, 4, 0, PM, LOGN> t0;
+  t0.load(tid, tw);
+  inv_pass<false>(x, t0, c, pk);
+  PassTw<10, 3, 7, 0, PM, LOGN> t1;
+  t1.load(tid, tw);
   exchange<3, 4, 7>(lds, x, tid);
-  inv_pass<10, 3, 7, 0, true, PM>(x, tid, tw, c, pk);
+  inv_pass<true>(x, t1, c, pk);
 #pragma unroll
   for (int k = 0; k < 8; k++) {
     const int v = tid + 128 * k;

@@ -3,8 +3,18 @@ and loaded in the mapping at bit 6, every exchange starts in the mapping in
 which the one before ended (each thread then overwrites only entries that it
 read itself, so one barrier orders a cross-wave exchange), and the padded
 LDS index of an element is that of the thread's part plus that of the
-register's, within the array, with no two elements at one place."""
+register's, within the array, with no two elements at one place.  Also the
+twiddle tables' order (csrc/tw_layout.h): every entry of a stage has a place of
+its own, and a stage read by lanes of different blocks puts the entries of 64
+consecutive blocks side by side."""
+import os
+import shutil
+import subprocess
+
 import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = "/opt/rocm/llvm/bin/clang++" if os.path.exists("/opt/rocm/llvm/bin/clang++") else shutil.which("clang++")
 
 
 def elem(loge, lo, t, k):
@@ -46,3 +56,35 @@ def test_exchange_chain(logn, loge):
                     block = set(range(w * 64 * e, (w + 1) * 64 * e))
                     assert {elem(loge, frm, t, k) for t in ts for k in range(e)} == block
                     assert {elem(loge, to, t, k) for t in ts for k in range(e)} == block
+
+
+TABLE_CHECK = """
+#include <cstdio>
+#include <vector>
+#include "tw_layout.h"
+int main() {
+  for (int n = 10; n <= 14; n++)
+    for (int s = 0; s < n; s++) {
+      std::vector<int> seen(1u << s, 0);
+      const int u = heconv::tw_u(n, s);
+      if (u > s) return std::printf("u %d %d", n, s), 1;
+      for (unsigned i = 0; i < 1u << s; i++) {
+        const unsigned p = heconv::tw_place(n, s, i);
+        if (p < 1u << s || p >= 2u << s || seen[p - (1u << s)]++) return std::printf("place %d %d %u", n, s, i), 1;
+        if (u && (i >> u) % 64 && p != heconv::tw_place(n, s, i - (1u << u)) + 1) return std::printf("run %d %d", n, s), 1;
+      }
+    }
+  std::printf("ok");
+}
+"""
+
+
+def test_twiddle_places(tmp_path):
+    if CXX is None:
+        pytest.skip("no clang++ for the host build")
+    src, out = tmp_path / "tw.cpp", tmp_path / "tw"
+    src.write_text(TABLE_CHECK)
+    subprocess.run([CXX, "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2506_11586_amd", "csrc"), str(src), "-o",
+                    str(out)], check=True)
+    r = subprocess.run([str(out)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout == "ok", r.stdout
