@@ -269,6 +269,16 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   }
   c->all_pm = true;
   for (const heconv::LimbConst& k : c->lc) c->all_pm &= k.pmd != 0;
+  for (uint32_t j = 0; j + 1 < L; j++) {
+    const uint64_t q = c->q[j], pi = mpow(c->q[L - 1] % q, q - 2, q);
+    c->pinv.v[j] = pi, c->pinv.sh[j] = shoup(pi, q);
+    if (!c->ntt_pm) continue;
+    const LimbConst& k = c->lc[j];
+    const uint32_t b = k.pb32 + 32;
+    c->ks.pinv[j] = twp_of(pi, q, b);
+    c->ks.ninv[j] = twp_of(mmul(k.ninv, pi, q), q, b);
+    c->ks.ninv_w[j] = twp_of(mmul(k.ninv_w, pi, q), q, b);
+  }
   // client-side decoding constants (power-of-two t only)
   std::vector<heconv::DecodeConst> dc(L);
   c->decode_ok = c->proto_ok && c->t >= 2 && c->t < (1ull << 62);
@@ -698,24 +708,38 @@ he_status ks_check(const he_ctx* ext, uint64_t n) {
   return HE_OK;
 }
 
+// From the transformed digits to the switched ciphertext: inner product,
+// inverse transform, division by P.  With the signed transforms and enough
+// ciphertexts the division rides on the transform (inner_moddown_launch: the
+// sums mod P first, then the rest), else a kernel of its own follows; the
+// sums mod P run alone first, so the rest must fill the chip by itself.
+// Rotation at N = 8192, L = 3, fused against not: 64 ciphertexts 82 against
+// 78 us, 128 131 against 146, 256 282 against 315.
+he_status ks_tail(const he_ctx* ext, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n, uint32_t nd,
+                  const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts, uint64_t w_stride, const uint64_t* ct,
+                  uint64_t* out, uint32_t ginv, const uint64_t* addp, hipStream_t st) {
+  const uint32_t L = ext->L - 1;
+  const uint64_t threads = n * L * 2 * (ext->N / 8);
+  if (ext->ntt_pm && threads >= 256 * 2048)  // 2048 threads a CU
+    return dev_err(heconv::inner_moddown_launch(ext->logN, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride,
+                                                ext->d_inv, ext->d_lc, ct, out, ginv, ext->ks, addp, st));
+  he_status s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride,
+                                                  ext->d_inv, ext->d_lc, ext->ntt_pm, st));
+  if (!s)
+    s = dev_err(heconv::moddown_launch(acc, ct, out, n, ext->N, L, ginv, ext->pinv, ext->d_lc, st, addp));
+  return s;
+}
+
 he_status ks_run(const he_ctx* ext, uint32_t ginv, uint64_t n, const uint64_t* ct, const uint64_t* ksk, uint64_t* out,
                  uint64_t* work, hipStream_t st, const uint64_t* addp = nullptr) {
   const uint32_t L = ext->L - 1, N = ext->N;
-  const uint64_t P = ext->q[L];
-  heconv::PinvConst pc{};
-  for (uint32_t j = 0; j < L; j++) {
-    const uint64_t q = ext->q[j];
-    pc.v[j] = mpow(P % q, q - 2, q);
-    pc.sh[j] = shoup(pc.v[j], q);
-  }
   uint64_t* digits = work;                                   // [n][L][L+1][N]
   uint64_t* acc = work + n * L * (uint64_t)(L + 1) * N;      // [n][2][L+1][N]
   he_status s = HE_OK;
   const bool fusable = heconv::ks_fwd_supported(ext->logN);
   if (ext->tune.ks_fused == 1 && fusable) {
     s = dev_err(heconv::modup_ntt_launch(ext->logN, ct, digits, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
-    if (!s) s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk, acc, n, L, L, nullptr, nullptr, 0, 0, ext->d_inv,
-                                                  ext->d_lc, ext->ntt_pm, st));
+    return s ? s : ks_tail(ext, digits, ksk, acc, n, L, nullptr, nullptr, 0, 0, ct, out, ginv, addp, st);
   } else {
     if (ext->tune.ks_fused == 2 && fusable) {
       s = dev_err(heconv::ks_fwd_launch(ext->logN, ct, ksk, acc, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
@@ -726,7 +750,7 @@ he_status ks_run(const he_ctx* ext, uint32_t ginv, uint64_t n, const uint64_t* c
     }
     if (!s) s = dev_err(ntt_run(ext, true, acc, 2 * n, st));
   }
-  if (!s) s = dev_err(heconv::moddown_launch(acc, ct, out, n, N, L, ginv, pc, ext->d_lc, st, addp));
+  if (!s) s = dev_err(heconv::moddown_launch(acc, ct, out, n, N, L, ginv, ext->pinv, ext->d_lc, st, addp));
   return s;
 }
 
@@ -905,13 +929,7 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
                  uint32_t n_diag, uint32_t groups, const uint64_t* ksk, uint32_t g2, const uint64_t* ksk2,
                  uint64_t* d_out, uint64_t* d_work, hipStream_t st) {
   const uint32_t L = ext->L - 1, N = ext->N, ginv = inv_mod_2n(g, N);
-  const uint64_t P = ext->q[L], ctw = 2ull * L * N;  // words per ciphertext
-  heconv::PinvConst pc{};
-  for (uint32_t j = 0; j < L; j++) {
-    const uint64_t q = ext->q[j];
-    pc.v[j] = mpow(P % q, q - 2, q);
-    pc.sh[j] = shoup(pc.v[j], q);
-  }
+  const uint64_t ctw = 2ull * L * N;  // words per ciphertext
   const uint64_t nc = n * groups;
   const uint32_t per = n_diag / groups;
   // work: two accumulators of nc ciphertexts, digits [nc][L][L+1][N], sums
@@ -930,10 +948,8 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
     he_status s = HE_OK;
     if (prev) s = dev_err(heconv::modup_ntt_launch(ext->logN, prev, digits, nc, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
     if (!s)
-      s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk, sums, nc, L, prev ? L : 0, d_x_ntt,
-                                            d_w + (uint64_t)i * L * N, n, (uint64_t)per * L * N, ext->d_inv,
-                                            ext->d_lc, ext->ntt_pm, st));
-    if (!s) s = dev_err(heconv::moddown_launch(sums, prev, next, nc, N, L, ginv, pc, ext->d_lc, st));
+      s = ks_tail(ext, digits, ksk, sums, nc, prev ? L : 0, d_x_ntt, d_w + (uint64_t)i * L * N, n, (uint64_t)per * L * N,
+                  prev, next, ginv, nullptr, st);
     if (s) return s;
     prev = next;
     cur ^= 1;
@@ -948,11 +964,8 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
     uint64_t* next = c == 0 ? d_out : tmp[c & 1];
     he_status s = dev_err(heconv::modup_ntt_launch(ext->logN, acc, digits, n, L, g2inv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
     if (!s)
-      s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk2, sums, n, L, L, nullptr, nullptr, 0, 0,
-                                            ext->d_inv, ext->d_lc, ext->ntt_pm, st));
-    if (!s)
-      s = dev_err(heconv::moddown_launch(sums, acc, next, n, N, L, g2inv, pc, ext->d_lc, st,
-                                         prev + (uint64_t)c * n * ctw));
+      s = ks_tail(ext, digits, ksk2, sums, n, L, nullptr, nullptr, 0, 0, acc, next, g2inv, prev + (uint64_t)c * n * ctw,
+                  st);
     if (s) return s;
     acc = next;
   }

@@ -30,6 +30,9 @@ struct he_ctx {
   void* d_fc = nullptr;       // per-limb F64Const
   bool decode_ok = false;
   heconv::LimbConst tlc{};  // reduction constants of t (decryption)
+  // key switching with the last prime as P (L >= 2)
+  heconv::PinvConst pinv{};
+  heconv::KsConst ks{};  // ntt_pm only
   he_tuning tune{3, 3, 512, 0, 0, 0, 1, 160, 1, 1, 128, 3, 0, 1};
   // internal stream and events of the output-channel pipeline of he_conv_layer
   hipStream_t aux = nullptr;

@@ -43,6 +43,11 @@ hipError_t ntt_f64_launch(bool inverse, uint32_t logN, uint32_t loge, uint64_t* 
 struct PinvConst {
   uint64_t v[7], sh[7];  // P^-1 mod q_j and its Shoup quotient, j < L (L <= 7)
 };
+// The same factors for the signed transforms: P^-1, and N^-1 * P^-1 with the
+// last inverse stage's second factor, mod q_j.
+struct KsConst {
+  TwP pinv[7], ninv[7], ninv_w[7];
+};
 hipError_t automorph_launch(const uint64_t* in, uint64_t* out, uint64_t rows, uint32_t N, uint32_t L, uint32_t ginv,
                             const LimbConst* lc, hipStream_t st);
 hipError_t modup_launch(const uint64_t* ct, uint64_t* work, uint64_t n, uint32_t N, uint32_t L, uint32_t ginv,
@@ -60,6 +65,13 @@ hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits,
 hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
                              uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
                              uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, bool pm, hipStream_t st);
+// The inner product, inverse transform and division by P in two kernels with
+// no stored sums but those mod P (signed transforms; modup_ntt's digits): the
+// arguments of inner_intt_launch and moddown_launch.
+hipError_t inner_moddown_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
+                                uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
+                                uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, const uint64_t* ct,
+                                uint64_t* out, uint32_t ginv, const KsConst& kc, const uint64_t* addp, hipStream_t st);
 hipError_t galois_key_launch(const uint64_t* work, uint64_t* ksk, uint32_t N, uint32_t L, const LimbConst* ext,
                              hipStream_t st);
 

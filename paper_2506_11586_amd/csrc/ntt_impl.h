@@ -169,7 +169,7 @@ constexpr int fwd_since(int P) {
 
 // Inverse stages u from LOGE-1 down to U0 of the pass at LO.  With LAST, the
 // stage on the top bit (u = 0 of the pass at n-LOGE) also applies N^-1 and
-// leaves canonical values.
+// leaves canonical values (RAW, PM only: signed ones below 0.9u).
 //
 // PM: with s and p for the sum and the product of a stage, an input bound a
 // <= 1.8u gives after two stages ss 4a = 7.2u, sp T(4a) = 1.0u, ps 2T(2a) =
@@ -180,7 +180,7 @@ constexpr int fwd_since(int P) {
 // canonical inputs brings its sums (2u) to 0.5u.  So every pass starts below
 // 1.8u again, and no value reaches 7.5u.  Register k's bit j is 0 where
 // stage j of the pass left it a sum.
-template <bool LAST, int LOGN, int LOGE, int LO, int U0, bool PM, int TLOGN>
+template <bool LAST, bool RAW = false, int LOGN, int LOGE, int LO, int U0, bool PM, int TLOGN>
 __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], const PassTw<LOGN, LOGE, LO, U0, PM, TLOGN>& tw,
                                          const LimbConst& c, const PmRegs& pk) {
   const uint64_t q3 = c.three_q;
@@ -193,8 +193,9 @@ __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LOGE], const PassTw<
         const int k0 = e, k1 = e + half;
         uint64_t X = x[k0], Y = x[k1];
         if constexpr (PM) {
-          x[k0] = pm_canon(pm_mul_val(X + Y, c.pninv, pk) + c.pk, c);
-          x[k1] = pm_canon(pm_mul_val(X - Y, c.pninv_w, pk) + c.pk, c);
+          x[k0] = pm_mul_val(X + Y, c.pninv, pk);
+          x[k1] = pm_mul_val(X - Y, c.pninv_w, pk);
+          if constexpr (!RAW) x[k0] = pm_canon(x[k0] + c.pk, c), x[k1] = pm_canon(x[k1] + c.pk, c);
         } else {
           x[k0] = csub_neg(mul_shoup_neg(X + Y, c.ninv, c.ninv_sh, c.negq), c.negq);
           x[k1] = csub_neg(mul_shoup_neg(X - Y + q3, c.ninv_w, c.ninv_w_sh, c.negq), c.negq);
@@ -293,7 +294,7 @@ __device__ __forceinline__ void fwd_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds
 
 // Inverse passes: the partial one at LO = 0 (P = -1, if any), then full ones
 // at LO = REM + LOGE*P, each after the exchange from the mapping at PREV.
-template <int LOGN, int LOGE, int P, int PREV, bool PM>
+template <int LOGN, int LOGE, int P, int PREV, bool PM, bool RAW>
 __device__ __forceinline__ void inv_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds, int tid,
                                          const Tw* __restrict__ tw, const LimbConst& c, const PmRegs& pk) {
   constexpr int NFULL = LOGN / LOGE, REM = LOGN % LOGE;
@@ -302,8 +303,8 @@ __device__ __forceinline__ void inv_rest(uint64_t (&x)[1 << LOGE], uint64_t* lds
     PassTw<LOGN, LOGE, LO, U0, PM> t;
     t.load(tid, tw);
     exchange<LOGE, PREV, LO>(lds, x, tid);
-    inv_pass<(P == NFULL - 1)>(x, t, c, pk);
-    inv_rest<LOGN, LOGE, P + 1, LO, PM>(x, lds, tid, tw, c, pk);
+    inv_pass<(P == NFULL - 1), RAW>(x, t, c, pk);
+    inv_rest<LOGN, LOGE, P + 1, LO, PM, RAW>(x, lds, tid, tw, c, pk);
   }
 }
 
@@ -340,13 +341,14 @@ __device__ __forceinline__ void ntt_fwd_poly(gword* __restrict__ a, const Tw* __
 
 // Inverse transform of NTT values already in registers in the mapping of
 // NTT-form words (register k = entry io_base + 64*k); leaves the
-// coefficients canonical in the top mapping (entry t + k*N/E).
-template <int LOGN, int LOGE, bool PM>
+// coefficients canonical in the top mapping (entry t + k*N/E).  RAW (PM
+// only): signed values of the coefficients times c.pninv * N, below 0.9u.
+template <int LOGN, int LOGE, bool PM, bool RAW = false>
 __device__ __forceinline__ void ntt_inv_regs(uint64_t (&x)[1 << LOGE], const Tw* __restrict__ tw, const LimbConst& c,
                                              uint64_t* lds, int tid) {
   constexpr int REM = LOGN % LOGE;
   const PmRegs pk = pm_regs(c);
-  inv_rest<LOGN, LOGE, (REM > 0 ? -1 : 0), 6, PM>(x, lds, tid, tw, c, pk);
+  inv_rest<LOGN, LOGE, (REM > 0 ? -1 : 0), 6, PM, RAW>(x, lds, tid, tw, c, pk);
 }
 
 // Inverse transform of one limb polynomial a[N] (in place).  With NT the

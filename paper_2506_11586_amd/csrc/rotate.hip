@@ -22,6 +22,7 @@
 #include "kernels.h"
 #include "mac_impl.h"
 #include "ntt_impl.h"
+#include "udiv.h"
 
 namespace heconv {
 
@@ -273,75 +274,198 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void modup_ntt_kern
   for (int k = 0; k < E; k++) out[64 * k] = x[k];
 }
 
-// Inner product fused into the inverse transform: one workgroup per
-// (ciphertext i, component c, extended modulus m) sums the L products of the
-// transformed digits with the key row (c, m) in 128 bits as it loads them,
-// reduces once, transforms back in registers and stores acc[i][c][m].  The
-// two workgroups that read the same digit rows run on the same XCD.  Grid:
-// ceil(n*(L+1)/8)*8*2 workgroups.
+// The point-wise sums of key switching for one workgroup (ciphertext i,
+// component comp, extended modulus m): x[k] = sum over l < nd of digit l times
+// the key row (comp, m) at word io_base + 64*k, plus the plaintext term,
+// reduced once.
 //
 // With a plaintext term (xp, wp non-null; the Z_P multiply-accumulate-rotate
 // step), the sum for a ciphertext modulus m < L also takes
 // xp[i][c][m] * wp[m]: the input ciphertext times a plaintext already
-// multiplied by -P mod q_m.  The term is 0 mod P, so the division by P in
-// moddown_kernel leaves the rotated ciphertext plus (x * plaintext) exactly.
-// nd digits are summed (L, or 0 when the rotated ciphertext is zero).  The
-// batch may hold several chains of chain_cts ciphertexts that share the
-// input x but take different weights: ciphertext i uses x[i % chain_cts]
-// and the plaintext at wp + (i / chain_cts) * w_stride.
+// multiplied by -P mod q_m.  The term is 0 mod P, so the division by P leaves
+// the rotated ciphertext plus (x * plaintext) exactly.  nd digits are summed
+// (L, or 0 when the rotated ciphertext is zero).  The batch may hold several
+// chains of chain_cts ciphertexts that share the input x but take different
+// weights: ciphertext i uses x[i % chain_cts] and the plaintext at
+// wp + (i / chain_cts) * w_stride.
+//
+// PM: the products of 30-bit halves in three accumulators (at most eight
+// terms: am stays below 2^64) and one short fold, left below 2^60 + 2^54;
+// else 128-bit sums (each product below 2^120) and a full reduction.
+struct InnerArgs {
+  const uint64_t *digits, *ksk, *xp, *wp;
+  uint64_t w_stride;
+  UDiv chain;  // by chain_cts
+  uint32_t chain_cts, L, nd;
+};
+
 template <int LOGN, bool PM>
-__global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_kernel(const uint64_t* __restrict__ digits,
-                                                                       const uint64_t* __restrict__ ksk,
-                                                                       uint64_t* __restrict__ acc, uint64_t n,
-                                                                       uint32_t L, uint32_t nd,
-                                                                       const uint64_t* __restrict__ xp,
-                                                                       const uint64_t* __restrict__ wp,
-                                                                       uint64_t chain_cts, uint64_t w_stride,
-                                                                       const Tw* __restrict__ tw_all,
-                                                                       const LimbConst* __restrict__ ext) {
+__device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g, uint64_t i, uint32_t comp, uint32_t m,
+                                           const LimbConst& c, int tid) {
+  constexpr int E = 8, N = 1 << LOGN;
+  const uint32_t L = g.L, L1 = L + 1;
+  const bool plain = g.xp && m < L;
+  const uint32_t terms = g.nd + (plain ? 1 : 0);
+  // Rows are read through buffer resources (the row base in scalar
+  // registers, the lane's byte offset fixed, the register's offset 64*k*8 a
+  // scalar), so a load costs no per-lane address arithmetic.
+  const uint32_t lane = (uint32_t)io_base<3>(tid) * 8;
+  const uint64_t* d0 = g.digits + (i * L * L1 + m) * N;
+  const uint64_t* k0 = g.ksk + ((uint64_t)comp * L1 + m) * N;
+  const uint64_t* dp = nullptr;
+  const uint64_t* kp = nullptr;
+  if (plain) {
+    const uint32_t chain = udiv((uint32_t)i, g.chain), ic = (uint32_t)i - chain * g.chain_cts;
+    dp = g.xp + (((uint64_t)ic * 2 + comp) * L + m) * N;
+    kp = g.wp + chain * g.w_stride + (uint64_t)m * N;
+  }
+  const auto rows = [&](uint32_t l, __amdgpu_buffer_rsrc_t& rd, __amdgpu_buffer_rsrc_t& rk) {
+    const bool dig = l < g.nd;
+    const uint64_t d = dig ? (uint64_t)(d0 + (uint64_t)l * L1 * N) : (uint64_t)dp;
+    const uint64_t k = dig ? (uint64_t)(k0 + (uint64_t)l * 2 * L1 * N) : (uint64_t)kp;
+    rd = mac_rsrc((const uint64_t*)uniform64(d), (uint64_t)N * 8);
+    rk = mac_rsrc((const uint64_t*)uniform64(k), (uint64_t)N * 8);
+  };
+  if constexpr (PM) {
+    // four points at a time: 24 accumulator registers, so that two 1024-thread
+    // workgroups fit a CU
+#pragma unroll
+    for (int h = 0; h < E; h += 4) {
+      uint64_t a00[4], am[4], a11[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) a00[k] = am[k] = a11[k] = 0;
+      for (uint32_t l = 0; l < terms; l++) {
+        __amdgpu_buffer_rsrc_t rd, rk;
+        rows(l, rd, rk);
+        uint64_t dv[4], kv[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          dv[k] = mac_load(rd, lane, (uint32_t)(64 * (h + k) * 8));
+          kv[k] = mac_load(rk, lane, (uint32_t)(64 * (h + k) * 8));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          const Half30 xs = split30(dv[k]), ws = split30(kv[k]);
+          a00[k] += (uint64_t)xs.lo * ws.lo;
+          am[k] += (uint64_t)xs.lo * ws.hi;
+          am[k] += (uint64_t)xs.hi * ws.lo;
+          a11[k] += (uint64_t)xs.hi * ws.hi;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; k++)
+        x[h + k] = fold3_pm<false>(a00[k], am[k], a11[k], (uint32_t)c.d60, (uint32_t)c.c30);
+    }
+  } else {
+    uint64_t hi[E], lo[E];
+#pragma unroll
+    for (int k = 0; k < E; k++) hi[k] = lo[k] = 0;
+    for (uint32_t l = 0; l < terms; l++) {
+      __amdgpu_buffer_rsrc_t rd, rk;
+      rows(l, rd, rk);
+#pragma unroll
+      for (int k = 0; k < E; k++) {
+        uint64_t ph, pl;
+        mul_wide(mac_load(rd, lane, (uint32_t)(64 * k * 8)), mac_load(rk, lane, (uint32_t)(64 * k * 8)), ph, pl);
+        lo[k] += pl;
+        hi[k] += ph + (lo[k] < pl);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < E; k++) x[k] = reduce128(hi[k], lo[k], c);
+  }
+}
+
+// Inner product fused into the inverse transform: one workgroup per
+// (ciphertext i, component c, extended modulus m) forms the sums as it loads
+// their operands, transforms back in registers and stores acc[i][c][m].  The
+// two workgroups that read the same digit rows run on the same XCD.  Grid:
+// ceil(n*(L+1)/8)*8*2 workgroups.
+//
+// ONLY_P: the sums mod P alone (grid ceil(n/8)*8*2), stored centred into
+// (-P/2, P/2] as inner_moddown_kernel takes them.
+template <int LOGN, bool PM, bool ONLY_P>
+__global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_kernel(
+    InnerArgs g, uint64_t* __restrict__ acc, uint64_t n, const Tw* __restrict__ tw_all,
+    const LimbConst* __restrict__ ext) {
   constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E;
   __shared__ uint64_t lds[N + N / 16];
-  const uint32_t L1 = L + 1;
+  const uint32_t L1 = g.L + 1, per = ONLY_P ? 1 : L1;
   const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
   const uint64_t im = (uint64_t)(slot / 2) * 8 + xcd;  // (i, m)
   const uint32_t comp = slot % 2;
-  if (im >= n * L1) return;  // the whole workgroup leaves before any barrier
-  const uint32_t m = (uint32_t)(im % L1);
-  const uint64_t i = im / L1;
+  if (im >= n * per) return;  // the whole workgroup leaves before any barrier
+  const uint32_t m = ONLY_P ? g.L : (uint32_t)(im % L1);
+  const uint64_t i = ONLY_P ? im : im / L1;
   const int tid = threadIdx.x;
   const LimbConst c = ext[m];
-  uint64_t hi[E], lo[E];
-#pragma unroll
-  for (int k = 0; k < E; k++) hi[k] = lo[k] = 0;
-  // L <= 7 digit products and one plaintext product, each below 2^120: the
-  // 128-bit sums do not overflow.  Rows are read through buffer resources
-  // (the row base in scalar registers, the lane's byte offset fixed, the
-  // register's offset 64*k*8 a scalar), so a load costs no per-lane address
-  // arithmetic.
-  const bool plain = xp && m < L;
-  const uint32_t lane = (uint32_t)io_base<LOGE>(tid) * 8;
-  for (uint32_t l = 0; l < nd + (plain ? 1 : 0); l++) {
-    const uint64_t* d =
-        l < nd ? digits + ((i * L + l) * L1 + m) * N : xp + (((i % chain_cts) * 2 + comp) * L + m) * N;
-    const uint64_t* kr =
-        l < nd ? ksk + ((uint64_t)(l * 2 + comp) * L1 + m) * N : wp + (i / chain_cts) * w_stride + (uint64_t)m * N;
-    const __amdgpu_buffer_rsrc_t rd = mac_rsrc((const uint64_t*)uniform64((uint64_t)d), (uint64_t)N * 8);
-    const __amdgpu_buffer_rsrc_t rk = mac_rsrc((const uint64_t*)uniform64((uint64_t)kr), (uint64_t)N * 8);
-#pragma unroll
-    for (int k = 0; k < E; k++) {
-      uint64_t ph, pl;
-      mul_wide(mac_load(rd, lane, (uint32_t)(64 * k * 8)), mac_load(rk, lane, (uint32_t)(64 * k * 8)), ph, pl);
-      lo[k] += pl;
-      hi[k] += ph + (lo[k] < pl);
-    }
-  }
   uint64_t x[E];
-#pragma unroll
-  for (int k = 0; k < E; k++) x[k] = reduce128(hi[k], lo[k], c);
+  inner_sums<LOGN, PM>(x, g, i, comp, m, c, tid);
   ntt_inv_regs<LOGN, LOGE, PM>(x, tw_all + (size_t)m * N, c, lds, tid);
   uint64_t* out = acc + ((i * 2 + comp) * L1 + m) * N;
 #pragma unroll
-  for (int k = 0; k < E; k++) out[tid + k * T] = x[k];
+  for (int k = 0; k < E; k++) out[tid + k * T] = ONLY_P && x[k] > c.q / 2 ? x[k] - c.q : x[k];
+}
+
+// The same for the ciphertext moduli m < L with the division by P after the
+// transform, in registers: with xc the centred residue mod P (acc[i][c][L],
+// from inner_intt_kernel<ONLY_P>), y = x*P^-1 - xc*P^-1 mod q_m, where the
+// factor P^-1 of x rides on the transform's last products; the stored sums
+// mod q_m and moddown_kernel's pass over them fall away.  b (component 1) is
+// read through the automorphism from the transform's LDS, staged with
+// coalesced loads.  Grid: ceil(n*L/8)*8*2 workgroups.  Signed transforms only.
+template <int LOGN>
+__global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_moddown_kernel(
+    InnerArgs g, const uint64_t* __restrict__ acc, uint64_t n, const Tw* __restrict__ tw_all,
+    const LimbConst* __restrict__ ext, const uint64_t* ct, uint64_t* out_, uint32_t ginv, KsConst kc,
+    const uint64_t* addp) {
+  constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E;
+  __shared__ uint64_t lds[N + N / 16];
+  const uint32_t L = g.L, L1 = L + 1;
+  const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
+  const uint64_t im = (uint64_t)(slot / 2) * 8 + xcd;  // (i, m)
+  const uint32_t comp = slot % 2;
+  if (im >= n * L) return;  // the whole workgroup leaves before any barrier
+  const uint32_t m = (uint32_t)(im % L);
+  const uint64_t i = im / L;
+  const int tid = threadIdx.x;
+  LimbConst c = ext[m];
+  c.pninv = kc.ninv[m], c.pninv_w = kc.ninv_w[m];
+  uint64_t x[E];
+  inner_sums<LOGN, true>(x, g, i, comp, m, c, tid);
+  ntt_inv_regs<LOGN, LOGE, true, true>(x, tw_all + (size_t)m * N, c, lds, tid);  // |x| < 0.9u
+  const PmRegs pk = pm_regs(c);
+  const uint64_t* xc = acc + ((i * 2 + comp) * L1 + L) * N + tid;
+  const TwP pinv = kc.pinv[m];
+#pragma unroll
+  for (int k = 0; k < E; k++) x[k] = pm_mul_val(xc[k * T], pinv, pk) - x[k];  // -y, |.| < 1.7u
+  const uint64_t row = ((i * 2 + comp) * L + m) * N;
+  if (comp && ct) {  // (null: a zero ciphertext)
+    const uint64_t* b = ct + row;
+    if (ginv == 1) {
+#pragma unroll
+      for (int k = 0; k < E; k++) x[k] += b[tid + k * T];
+    } else {
+      // the thread's own entries of the last exchange are rewritten, so only
+      // the gather needs a barrier
+#pragma unroll
+      for (int k = 0; k < E; k++) lds[lds_pad(tid + k * T)] = b[tid + k * T];
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < E; k++) {
+        const uint32_t src = (uint32_t)(((uint64_t)(tid + k * T) * ginv) & (2 * N - 1));
+        const uint64_t v = lds[lds_pad(src & (N - 1))];
+        x[k] += src >= (uint32_t)N ? 0 - v : v;
+      }
+    }
+  }
+  if (addp) {
+#pragma unroll
+    for (int k = 0; k < E; k++) x[k] += addp[row + tid + k * T];
+  }
+  uint64_t* out = out_ + row + tid;
+#pragma unroll
+  for (int k = 0; k < E; k++) out[k * T] = pm_canon(x[k] + c.pk, c);  // |x| < 3.7u
 }
 
 // Galois key for digit l and extended modulus m, in NTT form:
@@ -467,19 +591,63 @@ hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits,
   return hipGetLastError();
 }
 
+// (without a plaintext term, or as one chain, every ciphertext is its own)
+static InnerArgs inner_args(const uint64_t* digits, const uint64_t* ksk, const uint64_t* xp, const uint64_t* wp,
+                            uint64_t chain_cts, uint64_t w_stride, uint32_t L, uint32_t nd) {
+  const uint32_t cts = chain_cts && chain_cts < (1ull << 31) ? (uint32_t)chain_cts : 0x7fffffffu;
+  return InnerArgs{digits, ksk, xp, wp, w_stride, udiv_make(cts), cts, L, nd};
+}
+
 hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
                              uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
                              uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, bool pm, hipStream_t st) {
-  if (chain_cts == 0) chain_cts = n ? n : 1;
+  const InnerArgs g = inner_args(digits, ksk, xp, wp, chain_cts, w_stride, L, nd);
   const uint64_t blocks = (n * (L + 1) + 7) / 8 * 8 * 2;
   if (blocks > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;  // up to N/8 = 1024 threads
   if (!blocks) return hipSuccess;
   const dim3 grid((uint32_t)blocks);
+#define HECONV_INNER(LN)                                                                                           \
+  if (pm)                                                                                                          \
+    hipLaunchKernelGGL((inner_intt_kernel<LN, true, false>), grid, dim3((1u << LN) / 8), 0, st, g, acc, n, tw_inv, \
+                       ext);                                                                                       \
+  else                                                                                                             \
+    hipLaunchKernelGGL((inner_intt_kernel<LN, false, false>), grid, dim3((1u << LN) / 8), 0, st, g, acc, n,        \
+                       tw_inv, ext)
   switch (logN) {
-    case 10: HECONV_ROT(inner_intt_kernel, 10, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
-    case 11: HECONV_ROT(inner_intt_kernel, 11, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
-    case 12: HECONV_ROT(inner_intt_kernel, 12, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
-    case 13: HECONV_ROT(inner_intt_kernel, 13, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride, tw_inv, ext); break;
+    case 10: HECONV_INNER(10); break;
+    case 11: HECONV_INNER(11); break;
+    case 12: HECONV_INNER(12); break;
+    case 13: HECONV_INNER(13); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef HECONV_INNER
+  return hipGetLastError();
+}
+
+template <int LOGN>
+static void inner_moddown_go(const InnerArgs& g, uint64_t* acc, uint64_t n, const Tw* tw_inv, const LimbConst* ext,
+                             const uint64_t* ct, uint64_t* out, uint32_t ginv, const KsConst& kc, const uint64_t* addp,
+                             hipStream_t st) {
+  const dim3 t((1u << LOGN) / 8);
+  hipLaunchKernelGGL((inner_intt_kernel<LOGN, true, true>), dim3((uint32_t)((n + 7) / 8 * 8 * 2)), t, 0, st, g, acc, n,
+                     tw_inv, ext);
+  hipLaunchKernelGGL((inner_moddown_kernel<LOGN>), dim3((uint32_t)((n * g.L + 7) / 8 * 8 * 2)), t, 0, st, g, acc, n,
+                     tw_inv, ext, ct, out, ginv, kc, addp);
+}
+
+hipError_t inner_moddown_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
+                                uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
+                                uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, const uint64_t* ct,
+                                uint64_t* out, uint32_t ginv, const KsConst& kc, const uint64_t* addp,
+                                hipStream_t st) {
+  const InnerArgs g = inner_args(digits, ksk, xp, wp, chain_cts, w_stride, L, nd);
+  if ((n * L + 7) / 8 * 8 * 2 > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;
+  if (!n) return hipSuccess;
+  switch (logN) {
+    case 10: inner_moddown_go<10>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st); break;
+    case 11: inner_moddown_go<11>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st); break;
+    case 12: inner_moddown_go<12>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st); break;
+    case 13: inner_moddown_go<13>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

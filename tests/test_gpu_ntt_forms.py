@@ -92,3 +92,41 @@ def test_rotation_in_both_forms(kind, g, fused):
     out = empty_words(ct.size)
     ext.rotate(g, n, to_dev(ct), dk, out, empty_words(ext.keyswitch_work_words(n)))
     assert np.array_equal(to_host(out).reshape(ct.shape), oracle.rotate(ct, g, ksk, prm, P))
+
+
+@pytest.mark.parametrize("g", [1, 5])
+def test_division_by_P_inside_the_transform(g):
+    """A call large enough for the fused division by P: every ciphertext
+    against the same words rotated in a call too small for it, and the first
+    and the last against the oracle (digits and b words at their ends too)."""
+    N = 1024
+    ext, prm_all = context("near", N)
+    q, P = prm_all.q[:2], prm_all.q[2]
+    prm = oracle.Params(N, 2, 60, 2 ** 37, q=q)
+    sk = wl.secret_key(15, N)
+    a = synth.uniform_mod(Stream(16, synth.UNIFORM), (2, 3, N), prm_all.q)
+    e = Stream(16, synth.ERROR).cbd(2 * N, wl.ETA).reshape(2, N)
+    ksk = oracle.galois_key(sk, g, a, e, prm, P)
+    n = 256 * 2048 // (2 * 2 * (N // 8)) + 3  # first size of the fused form, and a remainder
+    ct = synth.uniform_mod(Stream(17, synth.UNIFORM), (n, 2, 2, N), q)
+    top = np.array(q, dtype=np.uint64)[:, None] - np.uint64(1)
+    ct[0] = top
+    ct[-1, 0], ct[-1, 1] = 0, top
+    dk = to_dev(ksk)
+    ext.ntt_fwd(dk, 4)
+    dct, out = to_dev(ct), empty_words(ct.size)
+    ext.rotate(g, n, dct, dk, out, empty_words(ext.keyswitch_work_words(n)))
+    got = to_host(out).reshape(ct.shape)
+    step = 64
+    for i in range(0, n, step):
+        m = min(step, n - i)
+        part, small = to_dev(ct[i:i + m]), empty_words(ct[i:i + m].size)
+        ext.rotate(g, m, part, dk, small, empty_words(ext.keyswitch_work_words(m)))
+        assert np.array_equal(got[i:i + m], to_host(small).reshape(ct[i:i + m].shape)), i
+    ends = [0, n - 1]
+    assert np.array_equal(got[ends], oracle.rotate(ct[ends], g, ksk, prm, P))
+    # rotate-and-add on the same path
+    ext.zp_fold(g, n, dct, dk, out, empty_words(ext.keyswitch_work_words(n)))
+    fold = to_host(out).reshape(ct.shape).astype(object)
+    want = (got.astype(object) + ct.astype(object)) % np.array(q, dtype=object)[:, None]
+    assert np.array_equal(fold, want)
