@@ -263,7 +263,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     if (f.ok) {
       k.pb32 = f.b - 32, k.pmask = (1u << k.pb32) - 1, k.pdelta = f.delta, k.d60 = (int32_t)f.d60;
       k.pk = q << (63 - f.b);
-      k.pninv = twp_of(k.ninv, q, f.b), k.pninv_w = twp_of(k.ninv_w, q, f.b);
+      k.pninv = twp_of(k.ninv, q, f.b), k.pninv_w = twp_of(k.ninv_w, q, f.b), k.tdelta = twp_of(k.delta, q, f.b);
     }
     c->lc.push_back(k);
   }
@@ -282,7 +282,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   // client-side decoding constants (power-of-two t only)
   std::vector<heconv::DecodeConst> dc(L);
   c->decode_ok = c->proto_ok && c->t >= 2 && c->t < (1ull << 62);
-  if (c->decode_ok) {
+  if (c->proto_ok) {
     const uint64_t t = c->t;
     c->tlc.q = t, c->tlc.two_q = 2 * t;
     c->tlc.r64 = (uint64_t)(((u128)1 << 64) % t), c->tlc.r64_sh = shoup(c->tlc.r64, t);
@@ -652,6 +652,13 @@ he_status he_encrypt(const he_ctx* c, uint64_t n, const int64_t* d_msgs, const u
   for (uint64_t i0 = 0; i0 < n; i0 += CLIENT_CHUNK) {
     const uint64_t m = n - i0 < CLIENT_CHUNK ? n - i0 : CLIENT_CHUNK;
     uint64_t* ct = d_ct + i0 * 2 * LN;
+    if (c->ntt_pm) {
+      if (he_status s = dev_err(heconv::client_product_launch(
+              true, c->logN, d_a + i0 * LN, d_sk_ntt, d_msgs + i0 * c->N, d_err + i0 * c->N, ct, m, c->L, c->tlc, c->d_fwd,
+              c->d_inv, c->d_lc, st)))
+        return s;
+      continue;
+    }
     he_status s = key_product(c, m, d_a + i0 * LN, LN, ct, d_sk_ntt, d_work, st);
     if (!s)
       s = dev_err(heconv::encrypt_finish_launch(d_work, d_msgs + i0 * c->N, d_err + i0 * c->N, ct, m, c->N, c->L,
@@ -672,9 +679,12 @@ he_status he_decrypt(const he_ctx* c, uint64_t n, const uint64_t* d_ct, const ui
   for (uint64_t i0 = 0; i0 < n; i0 += CLIENT_CHUNK) {
     const uint64_t m = n - i0 < CLIENT_CHUNK ? n - i0 : CLIENT_CHUNK;
     const uint64_t* ct = d_ct + i0 * 2 * LN;
-    he_status s = key_product(c, m, ct, 2 * LN, nullptr, d_sk_ntt, d_work, st);
+    he_status s = c->ntt_pm ? dev_err(heconv::client_product_launch(false, c->logN, ct, d_sk_ntt, nullptr, nullptr,
+                                                                    d_work, m, c->L, c->tlc, c->d_fwd, c->d_inv,
+                                                                    c->d_lc, st))
+                            : key_product(c, m, ct, 2 * LN, nullptr, d_sk_ntt, d_work, st);
     if (!s)
-      s = dev_err(heconv::decrypt_finish_launch(ct, d_work, d_msgs + i0 * c->N, m, c->N, c->L, c->tlc, c->d_dc,
+      s = dev_err(heconv::decrypt_finish_launch(c->ntt_pm ? nullptr : ct, d_work, d_msgs + i0 * c->N, m, c->N, c->L, c->tlc, c->d_dc,
                                                 c->d_lc, st));
     if (s) return s;
   }

@@ -12,7 +12,14 @@
 // fixed-point fraction (truncation error below L * 2^60 * 2^-128 in total);
 // the integer part is summed in 128 bits and reduced mod t at the end, so t
 // may be any modulus below 2^62 (a power of two or a prime).
+//
+// With the signed transforms (ntt_impl.h) the product is one kernel:
+// client_product_kernel keeps a polynomial in registers from the a word it
+// reads to the ciphertext word (or the phase word, for decryption) that it
+// writes.  The separate steps (copy, transform, point-wise product, inverse
+// transform, finish) serve the other primes.
 #include "kernels.h"
+#include "ntt_impl.h"
 
 namespace heconv {
 
@@ -82,7 +89,67 @@ __global__ __launch_bounds__(CLIENT_THREADS) void encrypt_finish_kernel(const ui
   ct[(i * 2 + 1) * L * N + j] = v;
 }
 
-// out[i][k] = round(t * V / Q) mod t, centred, with v_l = ct[i][1][l][k] - as[i][l][k].
+// a*sk for limb l of polynomial i, and what follows it, by one workgroup:
+// forward transform, product with the transformed key (three sums of 30-bit
+// halves and a short fold), inverse transform, all in registers and LDS.
+//  ENC: src = a [n][L][N]; ct[i][0] = a, ct[i][1] = a*sk + delta*(m mod t) + e.
+//  else: src = ct [n][2][L][N]; dst[i][l] = b - a*sk, the phase's residues.
+// Bound by the two transforms; its bytes are the inputs and outputs once (the
+// separate steps moved each polynomial nine times, six of them in passes of
+// their own): 64 encryptions and decryptions at N = 8192, L = 3 in 98 us
+// before, 10 launches.
+template <int LOGN, int LOGE, bool ENC>
+__global__ __launch_bounds__((1 << LOGN) >> LOGE, ntt_waves(LOGE)) void client_product_kernel(
+    const uint64_t* __restrict__ src, const uint64_t* __restrict__ sk_ntt, const int64_t* __restrict__ msg,
+    const int64_t* __restrict__ err, uint64_t* __restrict__ dst, uint32_t L, LimbConst tc,
+    const Tw* __restrict__ tw_fwd, const Tw* __restrict__ tw_inv, const LimbConst* __restrict__ lcs) {
+  constexpr int N = 1 << LOGN, E = 1 << LOGE, T = N / E;
+  __shared__ uint64_t lds[N + N / 16];
+  const uint32_t l = blockIdx.x % L;
+  const uint64_t i = blockIdx.x / L;
+  const int tid = threadIdx.x;
+  const LimbConst c = lcs[l];
+  const uint64_t* a = src + (ENC ? i * L + l : i * 2 * L + l) * N + tid;
+  uint64_t x[E];
+#pragma unroll
+  for (int k = 0; k < E; k++) x[k] = a[k * T];
+  if constexpr (ENC) {
+    uint64_t* ca = dst + (i * 2 * L + l) * N + tid;
+#pragma unroll
+    for (int k = 0; k < E; k++) ca[k * T] = x[k];
+  }
+  ntt_fwd_regs<LOGN, LOGE, true>(x, tw_fwd + (size_t)l * N, c, lds, tid);
+  const uint64_t* sk = sk_ntt + (size_t)l * N + io_base<LOGE>(tid);
+#pragma unroll
+  for (int k = 0; k < E; k++) {
+    const Half30 xs = split30(x[k]), ss = split30(sk[64 * k]);
+    const uint64_t am = (uint64_t)xs.lo * ss.hi + (uint64_t)xs.hi * ss.lo;
+    x[k] = fold3_pm<false>((uint64_t)xs.lo * ss.lo, am, (uint64_t)xs.hi * ss.hi, (uint32_t)c.d60, (uint32_t)c.c30);
+  }
+  ntt_inv_regs<LOGN, LOGE, true, true>(x, tw_inv + (size_t)l * N, c, lds, tid);  // a*sk, signed, below 0.9u
+  if constexpr (ENC) {
+    const PmRegs pk = pm_regs(c);
+    const TwP delta = c.tdelta;
+    uint64_t* b = dst + ((i * 2 + 1) * L + l) * N + tid;
+#pragma unroll
+    for (int k = 0; k < E; k++) {
+      const int64_t mv = msg[i * N + tid + k * T];
+      const uint64_t mag = mv < 0 ? 0ull - (uint64_t)mv : (uint64_t)mv;
+      const uint64_t r = csub(csub(reduce64_lazy(mag, tc.mu64, tc.q), tc.two_q), tc.q);
+      const uint64_t m = mv < 0 && r ? tc.q - r : r;
+      const uint64_t v = x[k] + pm_mul_val(m, delta, pk) + mod_q_signed_c(err[i * N + tid + k * T], c);
+      b[k * T] = pm_canon(v + c.pk, c);
+    }
+  } else {
+    const uint64_t* b = src + ((i * 2 + 1) * L + l) * N + tid;
+    uint64_t* v = dst + (i * L + l) * N + tid;
+#pragma unroll
+    for (int k = 0; k < E; k++) v[k * T] = pm_canon(b[k * T] - x[k] + c.pk, c);
+  }
+}
+
+// out[i][k] = round(t * V / Q) mod t, centred, with v_l = ct[i][1][l][k] - as[i][l][k]
+// (ct null: as holds v itself).
 __global__ __launch_bounds__(CLIENT_THREADS) void decrypt_finish_kernel(const uint64_t* __restrict__ ct,
                                                                          const uint64_t* __restrict__ as,
                                                                          int64_t* __restrict__ out, uint32_t N,
@@ -97,8 +164,8 @@ __global__ __launch_bounds__(CLIENT_THREADS) void decrypt_finish_kernel(const ui
   for (uint32_t l = 0; l < L; l++) {
     const LimbConst c = lcs[l];
     const DecodeConst d = dcs[l];
-    const uint64_t b = ct[((i * 2 + 1) * L + l) * N + k], a = as[(i * L + l) * N + k];
-    const uint64_t v = csub(b + (c.q - a), c.q);
+    const uint64_t a = as[(i * L + l) * N + k];
+    const uint64_t v = ct ? csub(ct[((i * 2 + 1) * L + l) * N + k] + (c.q - a), c.q) : a;
     uint64_t ph, pl;
     mul_wide(v, d.ipart, ph, pl);
     il += pl;
@@ -123,6 +190,36 @@ __global__ __launch_bounds__(CLIENT_THREADS) void decrypt_finish_kernel(const ui
   ih += il < r;
   const uint64_t m = reduce128(ih, il, tc);
   out[i * N + k] = m >= tc.q / 2 + (tc.q & 1) ? (int64_t)m - (int64_t)tc.q : (int64_t)m;
+}
+
+template <int LOGN, int LOGE>
+static hipError_t client_product_go(bool enc, const uint64_t* src, const uint64_t* sk_ntt, const int64_t* msg,
+                                    const int64_t* err, uint64_t* dst, uint64_t n, uint32_t L, const LimbConst& tc,
+                                    const Tw* twf, const Tw* twi, const LimbConst* lc, hipStream_t st) {
+  constexpr uint32_t T = (1u << LOGN) >> LOGE;
+  const uint64_t blocks = n * L;
+  if (blocks > grid_max_blocks(T)) return hipErrorInvalidConfiguration;
+  if (enc)
+    hipLaunchKernelGGL((client_product_kernel<LOGN, LOGE, true>), dim3((uint32_t)blocks), dim3(T), 0, st, src, sk_ntt,
+                       msg, err, dst, L, tc, twf, twi, lc);
+  else
+    hipLaunchKernelGGL((client_product_kernel<LOGN, LOGE, false>), dim3((uint32_t)blocks), dim3(T), 0, st, src, sk_ntt,
+                       msg, err, dst, L, tc, twf, twi, lc);
+  return hipGetLastError();
+}
+
+hipError_t client_product_launch(bool enc, uint32_t logN, const uint64_t* src, const uint64_t* sk_ntt,
+                                 const int64_t* msg, const int64_t* err, uint64_t* dst, uint64_t n, uint32_t L,
+                                 const LimbConst& tc, const Tw* twf, const Tw* twi, const LimbConst* lc,
+                                 hipStream_t st) {
+  switch (logN) {
+    case 10: return client_product_go<10, 3>(enc, src, sk_ntt, msg, err, dst, n, L, tc, twf, twi, lc, st);
+    case 11: return client_product_go<11, 3>(enc, src, sk_ntt, msg, err, dst, n, L, tc, twf, twi, lc, st);
+    case 12: return client_product_go<12, 3>(enc, src, sk_ntt, msg, err, dst, n, L, tc, twf, twi, lc, st);
+    case 13: return client_product_go<13, 3>(enc, src, sk_ntt, msg, err, dst, n, L, tc, twf, twi, lc, st);
+    case 14: return client_product_go<14, 4>(enc, src, sk_ntt, msg, err, dst, n, L, tc, twf, twi, lc, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 static dim3 grid_of(uint64_t words, uint64_t n) { return dim3((uint32_t)((words + CLIENT_THREADS - 1) / CLIENT_THREADS), (uint32_t)n); }

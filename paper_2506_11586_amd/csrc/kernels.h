@@ -165,6 +165,14 @@ hipError_t copy_a_launch(const uint64_t* src, uint64_t src_stride, uint64_t* wor
                          uint32_t N, uint32_t L, hipStream_t st);
 hipError_t pointwise_key_launch(uint64_t* work, const uint64_t* sk_ntt, uint64_t n, uint32_t N, uint32_t L,
                                 const LimbConst* lc, hipStream_t st);
+// The product with the key and what follows it in one kernel (signed
+// transforms): enc: src = a [n][L][N], dst = the ciphertexts; else src =
+// ciphertexts, dst = the phase residues b - a*sk [n][L][N] (decrypt_finish
+// then takes them with ct = null).  tc: reduction constants of t.
+hipError_t client_product_launch(bool enc, uint32_t logN, const uint64_t* src, const uint64_t* sk_ntt,
+                                 const int64_t* msg, const int64_t* err, uint64_t* dst, uint64_t n, uint32_t L,
+                                 const LimbConst& tc, const Tw* twf, const Tw* twi, const LimbConst* lc,
+                                 hipStream_t st);
 hipError_t encrypt_finish_launch(const uint64_t* as, const int64_t* msg, const int64_t* err, uint64_t* ct, uint64_t n,
                                  uint32_t N, uint32_t L, uint64_t t, const LimbConst* lc, hipStream_t st);
 hipError_t decrypt_finish_launch(const uint64_t* ct, const uint64_t* as, int64_t* out, uint64_t n, uint32_t N,

@@ -38,6 +38,7 @@ struct LimbConst {
   uint32_t pad_;
   uint64_t pk;                 // 2^(63 - pb) * q, the multiple of q next below 2^63
   TwP pninv, pninv_w;          // N^-1 and N^-1 * (last inverse twiddle)
+  TwP tdelta;                  // delta
 };
 
 // Device buffers are passed to the transform and MAC bodies as pointers in
