@@ -106,6 +106,9 @@ uint64_t shoup(uint64_t w, uint64_t q) { return (uint64_t)(((u128)w << 64) / q);
 // Shoup quotient at scale 2^63 (the transforms' twiddle tables).
 uint64_t shoup63(uint64_t w, uint64_t q) { return (uint64_t)(((u128)w << 63) / q); }
 
+// A residue as a double in (-q/2, q/2) (q < 2^50).
+double balanced(uint64_t w, uint64_t q) { return w > q / 2 ? -(double)(q - w) : (double)w; }
+
 // delta_l = floor(Q/t) mod q_l for Q = prod q_l, in multi-word arithmetic
 // (little-endian 64-bit words).  All zero when t is outside [2, 2^62] or
 // t > Q: the protocol steps then refuse to run.
@@ -306,20 +309,24 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   std::vector<unsigned char> fc;
   if (c->fp64_ok) {
     fwd64.resize((size_t)L * N), inv64.resize((size_t)L * N), fc.resize(heconv::f64_const_size() * L);
-    for (size_t i = 0; i < (size_t)L * N; i++) fwd64[i] = (double)fwd[i].w, inv64[i] = (double)inv[i].w;
     for (uint32_t l = 0; l < L; l++)
       heconv::f64_const_fill(fc.data() + heconv::f64_const_size() * l, (double)c->q[l], 1.0 / (double)c->q[l],
-                             (double)c->lc[l].ninv, (double)c->lc[l].ninv_w);
+                             balanced(c->lc[l].ninv, c->q[l]), balanced(c->lc[l].ninv_w, c->q[l]));
   }
-  // into the transforms' order of entries, and with ntt_pm the signed factors
+  // into the transforms' order of entries, the doubles from them, and with
+  // ntt_pm the signed factors
   std::vector<Tw> ord(N);
   for (uint32_t l = 0; l < L; l++)
-    for (Tw* tab : {fwd.data() + (size_t)l * N, inv.data() + (size_t)l * N}) {
+    for (int dir = 0; dir < 2; dir++) {
+      Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
+      double* tab64 = c->fp64_ok ? (dir ? inv64.data() : fwd64.data()) + (size_t)l * N : nullptr;
       ord[0] = tab[0];
       for (uint32_t st = 0; st < c->logN; st++) {
         for (uint32_t i = 0; i < (1u << st); i++) {
-          Tw& to = ord[heconv::tw_place((int)c->logN, (int)st, i)];
+          const uint32_t at = heconv::tw_place((int)c->logN, (int)st, i);
+          Tw& to = ord[at];
           to = tab[(1u << st) + i];
+          if (tab64) tab64[at] = balanced(to.w, c->q[l]);
           if (!c->ntt_pm) continue;
           const TwP p = twp_of(to.w, c->q[l], c->lc[l].pb32 + 32);
           std::memcpy(&to, &p, sizeof(Tw));

@@ -68,6 +68,13 @@ __device__ __forceinline__ uint64_t fwd_canon(uint64_t x, const LimbConst& c) {
   return canon_below6q(x, c.neg3q, c.neg2q, c.negq);
 }
 
+// Place of the twiddle that a thread of block `high` reads as the g-th of a
+// pass's stage u, stage s of the transform.
+template <int TLOGN>
+__device__ __forceinline__ uint32_t tw_at(int s, int u, uint32_t high, uint32_t g) {
+  return tw_u(TLOGN, s) == u && u ? tw_place_hg(s, u, high, g) : tw_place(TLOGN, s, (high << u) + g);
+}
+
 // The twiddles of a pass's stages [U0, LOGE) in the order the stages use them
 // (stage u holds 2^u of them from slot 2^u - 1 on; the inverse runs the stages
 // backwards over the same slots), at their places in the table (tw_layout.h).
@@ -91,11 +98,8 @@ struct PassTw {
     for (int u = U0; u < LOGE; u++) {
       const int s = LOGN - LOGE - LO + u;  // stage index
 #pragma unroll
-      for (int g = 0; g < (1 << u); g++) {
-        const uint32_t at =
-            tw_u(TLOGN, s) == u && u ? tw_place_hg(s, u, high, g) : tw_place(TLOGN, s, (high << u) + g);
-        t[(1 << u) - 1 + g] = reinterpret_cast<const T*>(tw)[at];
-      }
+      for (int g = 0; g < (1 << u); g++)
+        t[(1 << u) - 1 + g] = reinterpret_cast<const T*>(tw)[tw_at<TLOGN>(s, u, high, g)];
     }
   }
 };

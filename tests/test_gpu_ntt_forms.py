@@ -69,6 +69,36 @@ def test_transforms_in_both_forms(N, kind):
             assert np.array_equal(to_host(d).reshape(x.shape), inv), (loge, split)
 
 
+@pytest.mark.parametrize("bits", [50, 40])
+@pytest.mark.parametrize("N", [1024, 2048, 4096, 8192, 16384])
+def test_double_precision_transforms(N, bits):
+    """The fp64 transforms on words whose sums and differences are the
+    largest: all at the top, alternating ends in runs of every length."""
+    require_gpu()
+    ensure_built()
+    from paper_2506_11586_amd import heconv
+    q = oracle.find_primes(N, bits, 2)
+    ctx, prm = heconv.Context(N, q), oracle.Params(N, 2, bits, 2 ** 20, q=q)
+    top = np.array(q, dtype=np.uint64)[:, None] - np.uint64(1)
+    runs = [0, 1, 2, 3, N.bit_length() - 2]
+    x = synth.uniform_mod(Stream(N + 1, synth.UNIFORM), (len(runs) + 2, 2, N), q)
+    x[0] = top
+    for i, r in enumerate(runs):
+        x[i + 1] = np.where((np.arange(N) >> r) & 1, np.uint64(0), top)
+    n = x.shape[0]
+    fwd, inv = oracle.ntt(x, prm), oracle.intt(x, prm)
+    for loge in (3, 4):
+        ctx.set_tuning(ntt_loge_small=loge, ntt_loge_large=loge, ntt_fp64=1)
+        d = to_dev(x)
+        ctx.ntt_fwd(d, n)
+        assert np.array_equal(to_host(d).reshape(x.shape), fwd), loge
+        ctx.ntt_inv(d, n)
+        assert np.array_equal(to_host(d).reshape(x.shape), x), loge
+        d = to_dev(x)
+        ctx.ntt_inv(d, n)
+        assert np.array_equal(to_host(d).reshape(x.shape), inv), loge
+
+
 @pytest.mark.parametrize("kind", ["near", "delta24", "outside"])
 @pytest.mark.parametrize("g,fused", [(3, 1), (1, 1), (2 * 1024 - 1, 2)])
 def test_rotation_in_both_forms(kind, g, fused):
