@@ -65,12 +65,6 @@ bool pow2(uint64_t x) { return x && !(x & (x - 1)); }
 
 unsigned log2u(uint64_t x) { return 63 - __builtin_clzll(x); }
 
-unsigned bitrev(unsigned x, unsigned bits) {
-  unsigned r = 0;
-  for (unsigned i = 0; i < bits; i++, x >>= 1) r = (r << 1) | (x & 1);
-  return r;
-}
-
 // Products by one factor w < q < 2^62 without a division each: x*w mod q for
 // x < q by the factor's Shoup quotient.  (The root search and the tables are
 // chains of 3N products a limb; a 128-bit remainder each took most of
@@ -228,6 +222,8 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   c->proto_ok = std::all_of(dl.begin(), dl.end(), [](uint64_t v) { return v != 0; });
   std::vector<Tw> fwd((size_t)L * N), inv((size_t)L * N);
   std::vector<uint64_t> pw(N);
+  std::vector<uint32_t> brv(N);
+  for (uint32_t k = 1; k < N; k++) brv[k] = brv[k >> 1] >> 1 | (k & 1) << (c->logN - 1);
   for (uint32_t l = 0; l < L; l++) {
     const uint64_t q = c->q[l];
     const uint64_t psi = min_root(q, N);
@@ -244,7 +240,7 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
       for (uint32_t i = 1; i < N; i++) pw[i] = by(pw[i - 1]);
       Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
       for (uint32_t k = 0; k < N; k++) {
-        const uint64_t w = pw[bitrev(k, c->logN)];
+        const uint64_t w = pw[brv[k]];
         tab[k] = Tw{w, c->ntt_pm ? 0 : shoup63(w, q)};
       }
     }
