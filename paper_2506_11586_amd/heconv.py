@@ -185,9 +185,22 @@ def min_root(q: int, N: int) -> int:
     return int(out.value)
 
 
+_TORCH = None
+
+
+def _torch():
+    """torch, imported on first use (an import statement in every call costs
+    as much as the checks around it)."""
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
+
+
 def _ptr(t, words: int | None = None, what: str = "buffer") -> int:
     """Raw device pointer of a contiguous 64-bit-word CUDA tensor."""
-    import torch
+    torch = _torch()
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
@@ -204,8 +217,11 @@ def _ptr(t, words: int | None = None, what: str = "buffer") -> int:
 
 
 def _stream(stream) -> int:
-    import torch
     if stream is None:
+        torch = _torch()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch.cuda.current_device())  # without a Stream object: 0.5 against 2.9 us
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -268,6 +284,7 @@ class Context:
         h = ctypes.c_void_p()
         _check(lib().he_ctx_create(ctypes.byref(prm), ctypes.byref(h)), "he_ctx_create")
         self._h = h
+        self._sizes = {}  # descriptor values -> Sizes
         psi = (ctypes.c_uint64 * self.L)()
         _check(lib().he_ctx_psi(self._h, psi), "he_ctx_psi")
         self.psi = [int(v) for v in psi]
@@ -324,9 +341,22 @@ class Context:
                                    ctypes.byref(o), ctypes.byref(w)), "he_conv_sizes")
         return Sizes(CB.value, S.value, i.value, o.value, w.value)
 
+    def _sizes_of(self, d: ConvDesc) -> Sizes:
+        """sizes() for the layer calls' buffer checks, kept by the descriptor's
+        values (a few hundred of them): marshalling them anew took a quarter
+        of a small layer call's host time."""
+        key = bytes(d)
+        s = self._sizes.get(key)
+        if s is None:
+            s = self.sizes(d)
+            if len(self._sizes) >= 512:
+                self._sizes.clear()
+            self._sizes[key] = s
+        return s
+
     # -- the hot path ------------------------------------------------------
     def encode_weights(self, d: ConvDesc, w_dev, wntt_dev, stream=None):
-        s = self.sizes(d)
+        s = self._sizes_of(d)
         nw = d.M * d.C * d.kh * d.kw
         _check(lib().he_encode_weights(self._h, ctypes.byref(d), _ptr(w_dev, nw, "weights"),
                                        _ptr(wntt_dev, s.w_words, "wntt"), _stream(stream)), "he_encode_weights")
@@ -342,21 +372,21 @@ class Context:
                "he_ntt_inv")
 
     def conv_ntt_mac(self, d: ConvDesc, B: int, in_dev, wntt_dev, out_dev, stream=None):
-        s = self.sizes(d)
+        s = self._sizes_of(d)
         ct = 2 * self.L * self.N
         _check(lib().he_conv_ntt_mac(self._h, ctypes.byref(d), int(B), _ptr(in_dev, B * s.in_cts * ct, "in"),
                                      _ptr(wntt_dev, s.w_words, "wntt"), _ptr(out_dev, B * s.out_cts * ct, "out"),
                                      _stream(stream)), "he_conv_ntt_mac")
 
     def conv_mac_intt(self, d: ConvDesc, B: int, in_dev, wntt_dev, out_dev, stream=None):
-        s = self.sizes(d)
+        s = self._sizes_of(d)
         ct = 2 * self.L * self.N
         _check(lib().he_conv_mac_intt(self._h, ctypes.byref(d), int(B), _ptr(in_dev, B * s.in_cts * ct, "in"),
                                       _ptr(wntt_dev, s.w_words, "wntt"), _ptr(out_dev, B * s.out_cts * ct, "out"),
                                       _stream(stream)), "he_conv_mac_intt")
 
     def conv_layer(self, d: ConvDesc, B: int, in_dev, wntt_dev, out_dev, stream=None):
-        s = self.sizes(d)
+        s = self._sizes_of(d)
         ct = 2 * self.L * self.N
         _check(lib().he_conv_layer(self._h, ctypes.byref(d), int(B), _ptr(in_dev, B * s.in_cts * ct, "in"),
                                    _ptr(wntt_dev, s.w_words, "wntt"), _ptr(out_dev, B * s.out_cts * ct, "out"),
@@ -369,14 +399,14 @@ class Context:
 
     def add_share(self, d: ConvDesc, B: int, in_dev, share_dev, stream=None):
         """he_add_share: b_l += delta_l * pack(share) on the input cts (in place)."""
-        s = self.sizes(d)
+        s = self._sizes_of(d)
         _check(lib().he_add_share(self._h, ctypes.byref(d), int(B),
                                   _ptr(in_dev, B * s.in_cts * 2 * self.L * self.N, "in"),
                                   _ptr(share_dev, B * d.C * d.H * d.W, "share"), _stream(stream)), "he_add_share")
 
     def mask_extract(self, d: ConvDesc, B: int, out_dev, mask_dev, noise_dev, y_dev, stream=None):
         """he_mask_extract: y[b][m][l][oy][ox] = masked output coefficients."""
-        s = self.sizes(d)
+        s = self._sizes_of(d)
         Ho, Wo = self.out_hw(d)
         n = B * d.M * Ho * Wo
         _check(lib().he_mask_extract(self._h, ctypes.byref(d), int(B),
