@@ -220,7 +220,10 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
   if (c->ntt_pm) c->tune.ntt_split_below = c->tune.ntt_inv_split_below = c->logN == 14 ? 80 : 0;
   const std::vector<uint64_t> dl = deltas(c->q, c->t);
   c->proto_ok = std::all_of(dl.begin(), dl.end(), [](uint64_t v) { return v != 0; });
+  // double-precision transforms when every prime is below 2^50
+  c->fp64_ok = std::all_of(c->q.begin(), c->q.end(), [](uint64_t q) { return q < (1ull << 50); });
   std::vector<Tw> fwd((size_t)L * N), inv((size_t)L * N);
+  std::vector<double> fwd64(c->fp64_ok ? (size_t)L * N : 0), inv64(fwd64.size());
   std::vector<uint64_t> pw(N);
   std::vector<uint32_t> brv(N);
   for (uint32_t k = 1; k < N; k++) brv[k] = brv[k >> 1] >> 1 | (k & 1) << (c->logN - 1);
@@ -233,21 +236,37 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     }
     c->psi.push_back(psi);
     const uint64_t psi_inv = mpow(psi, q - 2, q);
+    uint64_t last_inv = 0;  // the last inverse stage's twiddle
     for (int dir = 0; dir < 2; dir++) {
       const uint64_t base = dir ? psi_inv : psi;
       pw[0] = 1;
       const MulBy by(base, q);
       for (uint32_t i = 1; i < N; i++) pw[i] = by(pw[i - 1]);
       Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
-      for (uint32_t k = 0; k < N; k++) {
-        const uint64_t w = pw[brv[k]];
-        tab[k] = Tw{w, c->ntt_pm ? 0 : shoup63(w, q)};
+      double* tab64 = c->fp64_ok ? (dir ? inv64.data() : fwd64.data()) + (size_t)l * N : nullptr;
+      // twiddle (high << u) + g of stage st is psi^brv(2^st + i), in the
+      // transforms' order of entries
+      for (uint32_t st = 0; st < c->logN; st++) {
+        const int u = heconv::tw_u((int)c->logN, (int)st);
+        for (uint32_t i = 0; i < (1u << st); i++) {
+          const uint64_t w = pw[brv[(1u << st) + i]];
+          const uint32_t at =
+              u ? heconv::tw_place_hg((int)st, u, i >> u, i & ((1u << u) - 1)) : (1u << st) + i;
+          if (tab64) tab64[at] = balanced(w, q);
+          if (c->ntt_pm) {
+            const TwP p = twp_of(w, q, log2u(q) + 1);
+            std::memcpy(&tab[at], &p, sizeof(Tw));
+          } else {
+            tab[at] = Tw{w, shoup63(w, q)};
+          }
+        }
       }
+      if (dir) last_inv = pw[brv[1]];
     }
     LimbConst k{};
     k.q = q, k.two_q = 2 * q;
     k.ninv = mpow(N % q, q - 2, q), k.ninv_sh = shoup(k.ninv, q);
-    k.ninv_w = mmul(k.ninv, inv[(size_t)l * N + 1].w, q), k.ninv_w_sh = shoup(k.ninv_w, q);
+    k.ninv_w = mmul(k.ninv, last_inv, q), k.ninv_w_sh = shoup(k.ninv_w, q);
     k.r64 = (uint64_t)(((u128)1 << 64) % q), k.r64_sh = shoup(k.r64, q), k.r64_sh63 = shoup63(k.r64, q);
     k.mu64 = (uint64_t)(((u128)1 << 64) / q);
     k.c30 = (uint64_t)(((u128)1 << 30) % q), k.c30_sh = shoup(k.c30, q);
@@ -266,8 +285,8 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     }
     c->lc.push_back(k);
   }
-  c->all_pm = true;
-  for (const heconv::LimbConst& k : c->lc) c->all_pm &= k.pmd != 0;
+  const bool all_60 = std::all_of(c->lc.begin(), c->lc.end(), [](const LimbConst& k) { return k.pmd != 0; });
+  c->mac_fold = all_60 ? heconv::MAC_FOLD_60 : (c->ntt_pm ? heconv::MAC_FOLD_PM : heconv::MAC_FOLD_ANY);
   for (uint32_t j = 0; j + 1 < L; j++) {
     const uint64_t q = c->q[j], pi = mpow(c->q[L - 1] % q, q - 2, q);
     c->pinv.v[j] = pi, c->pinv.sh[j] = shoup(pi, q);
@@ -299,37 +318,13 @@ he_status he_ctx_create(const he_params* prm, he_ctx** out) {
     const uint64_t fh = (uint64_t)(r64 / q), r2 = (uint64_t)(r64 % q);
     dc[l] = heconv::DecodeConst{(uint64_t)(ty / q), fh, (uint64_t)(((u128)r2 << 64) / q)};
   }
-  // double-precision transforms when every prime is below 2^50
-  c->fp64_ok = std::all_of(c->q.begin(), c->q.end(), [](uint64_t q) { return q < (1ull << 50); });
-  std::vector<double> fwd64, inv64;
   std::vector<unsigned char> fc;
   if (c->fp64_ok) {
-    fwd64.resize((size_t)L * N), inv64.resize((size_t)L * N), fc.resize(heconv::f64_const_size() * L);
+    fc.resize(heconv::f64_const_size() * L);
     for (uint32_t l = 0; l < L; l++)
       heconv::f64_const_fill(fc.data() + heconv::f64_const_size() * l, (double)c->q[l], 1.0 / (double)c->q[l],
                              balanced(c->lc[l].ninv, c->q[l]), balanced(c->lc[l].ninv_w, c->q[l]));
   }
-  // into the transforms' order of entries, the doubles from them, and with
-  // ntt_pm the signed factors
-  std::vector<Tw> ord(N);
-  for (uint32_t l = 0; l < L; l++)
-    for (int dir = 0; dir < 2; dir++) {
-      Tw* tab = (dir ? inv.data() : fwd.data()) + (size_t)l * N;
-      double* tab64 = c->fp64_ok ? (dir ? inv64.data() : fwd64.data()) + (size_t)l * N : nullptr;
-      ord[0] = tab[0];
-      for (uint32_t st = 0; st < c->logN; st++) {
-        for (uint32_t i = 0; i < (1u << st); i++) {
-          const uint32_t at = heconv::tw_place((int)c->logN, (int)st, i);
-          Tw& to = ord[at];
-          to = tab[(1u << st) + i];
-          if (tab64) tab64[at] = balanced(to.w, c->q[l]);
-          if (!c->ntt_pm) continue;
-          const TwP p = twp_of(to.w, c->q[l], c->lc[l].pb32 + 32);
-          std::memcpy(&to, &p, sizeof(Tw));
-        }
-      }
-      std::memcpy(tab, ord.data(), sizeof(Tw) * N);
-    }
   const size_t tb = sizeof(Tw) * (size_t)L * N;
   if (hipMalloc(&c->d_fwd, tb) != hipSuccess || hipMalloc(&c->d_inv, tb) != hipSuccess ||
       hipMalloc(&c->d_lc, sizeof(LimbConst) * L) != hipSuccess ||
@@ -511,7 +506,7 @@ he_status he_conv_ntt_mac(const he_ctx* c, const he_conv_desc* d, uint32_t B, co
   if (!d_in_ntt || !d_wntt || !d_out_ntt) return HE_EINVAL;
   if ((uint64_t)B * g.S * 2 > 0xffffffffull || !heconv::mac_offsets_fit(g, c->L, c->N)) return HE_ESHAPE;
   return dev_err(heconv::mac_launch(d_in_ntt, d_wntt, d_out_ntt, B, g.CB, g.S, d->M, c->L, c->N, c->d_lc,
-                                    c->tune.mac_mt, c->tune.mac_rt, c->tune.mac_lds, c->all_pm, c->tune.mac_grid != 0,
+                                    c->tune.mac_mt, c->tune.mac_rt, c->tune.mac_lds, c->mac_fold, c->tune.mac_grid != 0,
                                     (hipStream_t)stream));
 }
 
@@ -556,7 +551,7 @@ he_status he_conv_layer(const he_ctx* c, const he_conv_desc* d, uint32_t B, uint
     const uint32_t m_end = p + 1 == P ? d->M : (uint32_t)((uint64_t)d->M * (p + 1) / P) & ~3u;
     const uint32_t Mp = m_end - m0;
     s = dev_err(heconv::mac_launch(d_in, d_wntt + m0 * w_per_m, d_out + m0 * out_per_m, 1, g.CB, g.S, Mp, c->L,
-                                   c->N, c->d_lc, c->tune.mac_mt, c->tune.mac_rt, c->tune.mac_lds, c->all_pm,
+                                   c->N, c->d_lc, c->tune.mac_mt, c->tune.mac_rt, c->tune.mac_lds, c->mac_fold,
                                    c->tune.mac_grid != 0, st));
     if (s) return s;
     if (hipEventRecord(c->ev_mac[p], st) != hipSuccess || hipStreamWaitEvent(c->aux, c->ev_mac[p], 0) != hipSuccess)

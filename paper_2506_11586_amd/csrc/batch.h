@@ -58,7 +58,7 @@ struct BatchArgs {
   uint32_t loge_small, loge_large;  // NTT words per thread below / from 512 limb polys
   uint32_t mac_mt, mac_rt;          // MAC register tile, see batch_tile_supported
   uint32_t mac_lds;                 // 0, or LDS stages of the streamed MAC (mac_stream)
-  uint32_t all_pm;                  // every q_l = 2^60 - delta, delta < 2^20 (the MAC's short fold)
+  uint32_t mac_fold;                // the streamed MAC's fold for the context's primes (MacFold)
   uint32_t ntt_pm;                  // the twiddle tables are of the signed transforms (pm_mul)
   uint32_t mac_grid;                // streamed MAC on a 2x2 wave grid (mac_grid): tiles of 2*mac_mt x 2*mac_rt
 };

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(BATCH_MAC_THREADS) void batch_mac_kernel(const Batc
 }
 
 // Streamed MAC: workgroup b runs tiles mitems[b*per_wg ..] (see mac_stream).
-template <int MT, int RT, int P, bool PM>
+template <int MT, int RT, int P, int F>
 __global__ __launch_bounds__(BATCH_MAC_THREADS) void batch_mac_stream_kernel(const MacItem* __restrict__ items,
                                                                               uint32_t per_wg,
                                                                               const BatchJob* __restrict__ jobs,
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(BATCH_MAC_THREADS) void batch_mac_stream_kernel(con
                                                                               uint32_t L, uint32_t logN) {
   __shared__ uint64_t lds[mac_dma_lds_words<MT, RT, BATCH_MAC_THREADS, P>()];
   const MacListSrc src{items + (uint64_t)blockIdx.x * per_wg, per_wg, jobs};
-  mac_stream<MT, RT, BATCH_MAC_THREADS, P, PM>(src, lcs, L, logN, lds, threadIdx.x);
+  mac_stream<MT, RT, BATCH_MAC_THREADS, P, F>(src, lcs, L, logN, lds, threadIdx.x);
 }
 
 template <int LOGN, int LOGE, bool PM>
@@ -117,7 +117,7 @@ static hipError_t mac_regs(const BatchPhase& p, const BatchArgs& a, hipStream_t 
 
 // Streamed MAC on a 2x2 wave grid: workgroup b runs tiles mitems[b*per_wg ..]
 // (see mac_grid).
-template <int MT, int RT, int P, bool PM>
+template <int MT, int RT, int P, int F>
 __global__ __launch_bounds__(BATCH_MAC_THREADS) void batch_mac_grid_kernel(const MacItem* __restrict__ items,
                                                                             uint32_t per_wg,
                                                                             const BatchJob* __restrict__ jobs,
@@ -125,23 +125,27 @@ __global__ __launch_bounds__(BATCH_MAC_THREADS) void batch_mac_grid_kernel(const
                                                                             uint32_t L, uint32_t logN) {
   __shared__ uint64_t lds[P * MacGridShape<MT, RT>::ROWS * 64];
   const MacListSrc src{items + (uint64_t)blockIdx.x * per_wg, per_wg, jobs};
-  mac_grid<MT, RT, BATCH_MAC_THREADS, P, PM>(src, lcs, L, logN, lds, threadIdx.x);
+  mac_grid<MT, RT, BATCH_MAC_THREADS, P, F>(src, lcs, L, logN, lds, threadIdx.x);
+}
+
+template <int MT, int RT, int P, int F>
+static void mac_streamed_f(const BatchPhase& p, const BatchArgs& a, hipStream_t st) {
+  if (a.mac_grid)
+    hipLaunchKernelGGL((batch_mac_grid_kernel<MT, RT, P, F>), dim3(p.n), dim3(BATCH_MAC_THREADS), 0, st, p.mitems,
+                       p.per_wg, a.jobs, a.lcs, a.L, a.logN);
+  else
+    hipLaunchKernelGGL((batch_mac_stream_kernel<MT, RT, P, F>), dim3(p.n), dim3(BATCH_MAC_THREADS), 0, st, p.mitems,
+                       p.per_wg, a.jobs, a.lcs, a.L, a.logN);
 }
 
 template <int MT, int RT, int P>
 static void mac_streamed_p(const BatchPhase& p, const BatchArgs& a, hipStream_t st) {
-  if (a.mac_grid && a.all_pm)
-    hipLaunchKernelGGL((batch_mac_grid_kernel<MT, RT, P, true>), dim3(p.n), dim3(BATCH_MAC_THREADS), 0, st, p.mitems,
-                       p.per_wg, a.jobs, a.lcs, a.L, a.logN);
-  else if (a.mac_grid)
-    hipLaunchKernelGGL((batch_mac_grid_kernel<MT, RT, P, false>), dim3(p.n), dim3(BATCH_MAC_THREADS), 0, st,
-                       p.mitems, p.per_wg, a.jobs, a.lcs, a.L, a.logN);
-  else if (a.all_pm)
-    hipLaunchKernelGGL((batch_mac_stream_kernel<MT, RT, P, true>), dim3(p.n), dim3(BATCH_MAC_THREADS), 0, st, p.mitems,
-                       p.per_wg, a.jobs, a.lcs, a.L, a.logN);
+  if (a.mac_fold == MAC_FOLD_60)
+    mac_streamed_f<MT, RT, P, MAC_FOLD_60>(p, a, st);
+  else if (a.mac_fold == MAC_FOLD_PM)
+    mac_streamed_f<MT, RT, P, MAC_FOLD_PM>(p, a, st);
   else
-    hipLaunchKernelGGL((batch_mac_stream_kernel<MT, RT, P, false>), dim3(p.n), dim3(BATCH_MAC_THREADS), 0, st,
-                       p.mitems, p.per_wg, a.jobs, a.lcs, a.L, a.logN);
+    mac_streamed_f<MT, RT, P, MAC_FOLD_ANY>(p, a, st);
 }
 
 template <int MT, int RT>

@@ -66,7 +66,7 @@ heconv::BatchArgs args_of(const he_batch* b) {
   const he_ctx* c = b->ctx;
   return heconv::BatchArgs{b->d_jobs, c->d_fwd, c->d_inv, c->d_lc, c->L, c->N, c->logN,
                            c->tune.ntt_loge_small, c->tune.ntt_loge_large, b->mac_mt, b->mac_rt, b->mac_lds,
-                           c->all_pm ? 1u : 0u, c->ntt_pm ? 1u : 0u, b->mac_grid};
+                           c->mac_fold, c->ntt_pm ? 1u : 0u, b->mac_grid};
 }
 
 bool pipelined(const he_batch* b) { return b->schedule == HE_SCHED_PIPELINED_4 || b->schedule == HE_SCHED_PIPELINED_8; }

@@ -112,7 +112,7 @@ __device__ __forceinline__ void mac_grid_decode(const MacItem& it, const BatchJo
   }
 }
 
-template <int MT, int RT, int THREADS, int P, bool PM, class Src>
+template <int MT, int RT, int THREADS, int P, int F, class Src>
 __device__ __forceinline__ void mac_grid(const Src& src, const LimbConst* __restrict__ lcs, uint32_t L, uint32_t logN,
                                          uint64_t* lds, int tid) {
   static_assert(THREADS == 256 && MT % 2 == 0 && RT % 2 == 0 && P >= 2 && P <= 4, "four waves, rows in pairs");
@@ -215,8 +215,7 @@ __device__ __forceinline__ void mac_grid(const Src& src, const LimbConst* __rest
       for (int j = 0; j < MT; j++)
 #pragma unroll
         for (int i = 0; i < RT; i++) {
-          const uint64_t x = PM ? fold3_pm<false>(a00[j][i], am[j][i], a11[j][i], (uint32_t)c.pmd, (uint32_t)c.c30)
-                                : fold30(a00[j][i], am[j][i], 0, a11[j][i], c);
+          const uint64_t x = mac_fold_of<F, false>(a00[j][i], am[j][i], a11[j][i], c);
           a00[j][i] = x, am[j][i] = 0, a11[j][i] = 0;
         }
     }
@@ -224,8 +223,7 @@ __device__ __forceinline__ void mac_grid(const Src& src, const LimbConst* __rest
     for (int j = 0; j < MT; j++)
 #pragma unroll
       for (int i = 0; i < RT; i++) {
-        const uint64_t r = PM ? fold3_pm<true>(a00[j][i], am[j][i], a11[j][i], (uint32_t)c.pmd, (uint32_t)c.c30)
-                              : fold30(a00[j][i], am[j][i], 0, a11[j][i], c);
+        const uint64_t r = mac_fold_of<F, true>(a00[j][i], am[j][i], a11[j][i], c);
         if (((sd.rvalid >> i) & (sd.mvalid >> j) & 1u) != 0) {
           gword* o = out + uniform64(sd.obase[i / 2] + (uint64_t)(i & 1) * (LN8 / 8) + (uint64_t)j * sd.mstride);
           __builtin_nontemporal_store(r, &o[lane]);

@@ -123,11 +123,18 @@ struct MacOneSrc {
   __device__ __forceinline__ void get(uint32_t, MacItem& i, BatchJob& j) const { i = it, j = jd; }
 };
 
-// The source's tiles, for the calling wave's 64 points of each.  PM: every
-// limb's prime is 2^60 - delta (fold3_pm), else the Shoup fold of any prime
-// (fold30); a compile-time choice, so that the fold code has one path and
+template <int F, bool CANON>
+__device__ __forceinline__ uint64_t mac_fold_of(uint64_t a00, uint64_t am, uint64_t a11, const LimbConst& c) {
+  if constexpr (F == MAC_FOLD_ANY)
+    return fold30(a00, am, 0, a11, c);
+  else
+    return mac_fold<F, CANON>(a00, am, a11, c);
+}
+
+// The source's tiles, for the calling wave's 64 points of each.  F: the fold
+// of the limbs' primes (MacFold); a compile-time choice, so that the fold code has one path and
 // the accumulators stay in their registers across it.
-template <int MT, int RT, int THREADS, int P, bool PM, class Src>
+template <int MT, int RT, int THREADS, int P, int F, class Src>
 __device__ __forceinline__ void mac_stream(const Src& src, const LimbConst* __restrict__ lcs, uint32_t L,
                                            uint32_t logN, uint64_t* lds, int tid) {
   static_assert(MT % 2 == 0 && RT % 2 == 0 && P >= 2 && P <= 4, "rows are loaded in pairs");
@@ -227,8 +234,7 @@ __device__ __forceinline__ void mac_stream(const Src& src, const LimbConst* __re
       for (int j = 0; j < MT; j++)
 #pragma unroll
         for (int i = 0; i < RT; i++) {
-          const uint64_t x = PM ? fold3_pm<false>(a00[j][i], am[j][i], a11[j][i], (uint32_t)c.pmd, (uint32_t)c.c30)
-                                : fold30(a00[j][i], am[j][i], 0, a11[j][i], c);
+          const uint64_t x = mac_fold_of<F, false>(a00[j][i], am[j][i], a11[j][i], c);
           a00[j][i] = x, am[j][i] = 0, a11[j][i] = 0;
         }
     }
@@ -238,8 +244,7 @@ __device__ __forceinline__ void mac_stream(const Src& src, const LimbConst* __re
     for (int j = 0; j < MT; j++)
 #pragma unroll
       for (int i = 0; i < RT; i++) {
-        const uint64_t r = PM ? fold3_pm<true>(a00[j][i], am[j][i], a11[j][i], (uint32_t)c.pmd, (uint32_t)c.c30)
-                              : fold30(a00[j][i], am[j][i], 0, a11[j][i], c);
+        const uint64_t r = mac_fold_of<F, true>(a00[j][i], am[j][i], a11[j][i], c);
         if (((sd.rvalid >> i) & (sd.mvalid >> j) & 1u) != 0) {
           gword* o = out + uniform64(sd.obase[i / 2] + (uint64_t)(i & 1) * (LN8 / 8) + (uint64_t)j * sd.mstride);
           __builtin_nontemporal_store(r, &o[lane]);

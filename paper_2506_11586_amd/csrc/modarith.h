@@ -320,4 +320,25 @@ __device__ __forceinline__ uint64_t fold30(uint64_t a00, uint64_t a01, uint64_t 
   return csub(r, c.q);
 }
 
+// How the streamed MAC folds its three accumulators (MacFold of a context).
+enum MacFold {
+  MAC_FOLD_ANY = 0,  // any primes: fold30
+  MAC_FOLD_60 = 1,   // every q = 2^60 - delta, delta < 2^20: fold3_pm
+  MAC_FOLD_PM = 2    // every q of the signed transforms' form: fold3_pm with 2^60 = d60, then pm_canon
+};
+
+// MAC_FOLD_PM: with q < 2^b the halves' products are smaller as d60 is
+// larger, so that V*d60 of fold3_pm stays below 2^87 and its result below
+// 2^60 + 2^52 for any b; eight more blocks fit on top of it as they do on
+// 2^60 + 2^45.
+template <int F, bool CANON>
+__host__ __device__ __forceinline__ uint64_t mac_fold(uint64_t a00, uint64_t am, uint64_t a11, const LimbConst& c) {
+  if constexpr (F == MAC_FOLD_60) {
+    return fold3_pm<CANON>(a00, am, a11, (uint32_t)c.pmd, (uint32_t)c.c30);
+  } else {
+    const uint64_t x = fold3_pm<false>(a00, am, a11, (uint32_t)c.d60, (uint32_t)c.c30);
+    return CANON ? pm_canon(x, c) : x;
+  }
+}
+
 }  // namespace heconv

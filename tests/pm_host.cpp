@@ -3,7 +3,8 @@
 // and stays within T(|x|) = 0.766 * 2^60 + 0.0333 |x| for |x| up to 7.9 *
 // 2^60; pm_red within 0.5 * 2^60 + 8 * d60 for |x| < 7.5 * 2^60; pm_canon the
 // canonical residue; and both directions' passes, run on the stages and
-// reductions that ntt_impl.h states, never leave their bounds.
+// reductions that ntt_impl.h states, never leave their bounds; mac_fold over
+// chunks of the MAC's products.
 // Usage: pm_host <q> <trials>; prints "ok <n>" or the first failure, exit 1.
 #include <cstdio>
 #include <cstdlib>
@@ -52,6 +53,7 @@ int main(int argc, char** argv) {
   c.q = q, c.two28 = 1u << 28;
   c.pb32 = f.b - 32, c.pmask = (1u << c.pb32) - 1, c.pdelta = f.delta, c.d60 = (int32_t)f.d60;
   c.pk = q << (63 - f.b);
+  c.c30 = 1u << 30;
   const PmRegs k = pm_regs(c);
   const int64_t top = (int64_t)(7.9 * U), redtop = (int64_t)(7.49 * U);
   for (long n = 0; n < trials; n++) {
@@ -141,6 +143,23 @@ int main(int argc, char** argv) {
         if (pm_canon((uint64_t)x[i] + c.pk, c) != e[i]) return fail("inverse canonical", x[i], 0);
       }
       start = 1.8;
+    }
+  }
+  // the MAC's folds: chunks of eight products of residues (at their ends too) on a carried value
+  for (long n = 0; n < trials / 16; n++) {
+    uint64_t a00 = 0, am = 0, a11 = 0, want = 0;
+    for (int chunk = 0; chunk < 3; chunk++) {
+      for (int i = 0; i < 8; i++) {
+        const uint64_t x = n % 3 == 0 ? q - 1 : factor(n + i), w = n % 2 == 0 ? q - 1 : factor(n + 2 * i + 1);
+        const uint64_t xl = x & 0x3fffffff, xh = x >> 30, wl = w & 0x3fffffff, wh = w >> 30;
+        if ((u128)a00 + (u128)xl * wl >> 64 || (u128)am + (u128)xl * wh + (u128)xh * wl >> 64)
+          return fail("MAC accumulator", (int64_t)x, w);
+        a00 += xl * wl, am += xl * wh + xh * wl, a11 += xh * wh;
+        want = (want + mul(x, w)) % q;
+      }
+      if (mac_fold<MAC_FOLD_PM, true>(a00, am, a11, c) != want) return fail("mac_fold canonical", (int64_t)a00, am);
+      a00 = mac_fold<MAC_FOLD_PM, false>(a00, am, a11, c), am = a11 = 0;
+      if (a00 % q != want || a00 >= (1ull << 60) + (1ull << 52)) return fail("mac_fold carried", (int64_t)a00, 0);
     }
   }
   std::printf("ok %ld\n", trials);

@@ -160,3 +160,26 @@ def test_division_by_P_inside_the_transform(g):
     fold = to_host(out).reshape(ct.shape).astype(object)
     want = (got.astype(object) + ct.astype(object)) % np.array(q, dtype=object)[:, None]
     assert np.array_equal(fold, want)
+
+
+@pytest.mark.parametrize("kind", ["near", "delta24", "outside"])
+@pytest.mark.parametrize("C,M,B,grid", [(3, 5, 1, 0), (8, 9, 4, 1), (9, 8, 5, 1), (17, 17, 4, 0)])
+def test_mac_folds(kind, C, M, B, grid):
+    """The streamed MAC with each of its folds: channel blocks below, at and
+    above one chunk, the wave grid and the per-wave form, remainders of rows
+    and channels, words at their ends."""
+    N = 1024
+    ctx, prm = context(kind, N)
+    ctx.set_tuning(mac_grid=grid)
+    cv = wl.conv_of((C, 8, 8, M, 3, 3, 1, 1))
+    d = ctx.plan((C, 8, 8, M, 3, 3, 1, 1), batch=B, packing=(1, 10, 10))
+    g = oracle.geometry(cv, 1, 10, 10)
+    assert g.CB == C and g.S == 1
+    top = np.array(prm.q, dtype=np.uint64)[:, None] - np.uint64(1)
+    x = synth.uniform_mod(Stream(31, synth.UNIFORM), (B * C * 2, 3, N), prm.q)
+    w = synth.uniform_mod(Stream(32, synth.UNIFORM), (M * C, 3, N), prm.q)
+    x[:C * 2], w[:C] = top, top  # image 0 and channel 0: every product the largest
+    out = empty_words(B * M * 2 * 3 * N)
+    ctx.conv_ntt_mac(d, B, to_dev(x), to_dev(w), out)
+    want = oracle.conv_mac(x.reshape(B, C, 1, 2, 3, N), w.reshape(M, C, 3, N), B, g, M, prm)
+    assert np.array_equal(to_host(out).reshape(want.shape), want)
