@@ -291,7 +291,8 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void modup_ntt_kern
 //
 // PM: the products of 30-bit halves in three accumulators (at most eight
 // terms: am stays below 2^64) and one short fold, left below 2^60 + 2^54;
-// else 128-bit sums (each product below 2^120) and a full reduction.
+// else 128-bit sums (each product below 2^120) and a full reduction.  TERMS:
+// the number of terms where it is known (0: any).
 struct InnerArgs {
   const uint64_t *digits, *ksk, *xp, *wp;
   uint64_t w_stride;
@@ -299,7 +300,7 @@ struct InnerArgs {
   uint32_t chain_cts, L, nd;
 };
 
-template <int LOGN, bool PM>
+template <int LOGN, bool PM, int TERMS, int AHEAD = 2>
 __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g, uint64_t i, uint32_t comp, uint32_t m,
                                            const LimbConst& c, int tid) {
   constexpr int E = 8, N = 1 << LOGN;
@@ -326,9 +327,47 @@ __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g,
     rd = mac_rsrc((const uint64_t*)uniform64(d), (uint64_t)N * 8);
     rk = mac_rsrc((const uint64_t*)uniform64(k), (uint64_t)N * 8);
   };
-  if constexpr (PM) {
-    // four points at a time: 24 accumulator registers, so that two 1024-thread
-    // workgroups fit a CU
+  if constexpr (PM && TERMS > 0) {
+    // Two points at a time, and the operands of AHEAD steps (a step: one term of
+    // two points) in flight while one is multiplied: the rows come from beyond
+    // L2, and with the loads waited for step by step the waves were idle for
+    // half their time (rotation of 256 ciphertexts 271 -> 248 us).  With two
+    // steps ahead 12 accumulator and 24 operand registers stand beside x.
+    constexpr int G = 2, STEPS = E / G * TERMS;
+    uint64_t dv[AHEAD + 1][G], kv[AHEAD + 1][G];
+    __amdgpu_buffer_rsrc_t rd[TERMS], rk[TERMS];
+#pragma unroll
+    for (int l = 0; l < TERMS; l++) rows(l, rd[l], rk[l]);
+    const auto issue = [&](int st) {
+#pragma unroll
+      for (int k = 0; k < G; k++) {
+        const uint32_t off = (uint32_t)(64 * (st / TERMS * G + k) * 8);
+        dv[st % (AHEAD + 1)][k] = mac_load(rd[st % TERMS], lane, off);
+        kv[st % (AHEAD + 1)][k] = mac_load(rk[st % TERMS], lane, off);
+      }
+    };
+#pragma unroll
+    for (int st = 0; st < AHEAD && st < STEPS; st++) issue(st);
+    uint64_t a00[G], am[G], a11[G];
+#pragma unroll
+    for (int st = 0; st < STEPS; st++) {
+      if (st + AHEAD < STEPS) issue(st + AHEAD);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < G; k++) {
+        if (st % TERMS == 0) a00[k] = am[k] = a11[k] = 0;
+        const Half30 xs = split30(dv[st % (AHEAD + 1)][k]), ws = split30(kv[st % (AHEAD + 1)][k]);
+        a00[k] += (uint64_t)xs.lo * ws.lo;
+        am[k] += (uint64_t)xs.lo * ws.hi;
+        am[k] += (uint64_t)xs.hi * ws.lo;
+        a11[k] += (uint64_t)xs.hi * ws.hi;
+        if (st % TERMS == TERMS - 1)
+          x[st / TERMS * G + k] = fold3_pm<false>(a00[k], am[k], a11[k], (uint32_t)c.d60, (uint32_t)c.c30);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else if constexpr (PM) {
+    // any number of terms: four points at a time, 24 accumulator registers
 #pragma unroll
     for (int h = 0; h < E; h += 4) {
       uint64_t a00[4], am[4], a11[4];
@@ -382,10 +421,12 @@ __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g,
 // two workgroups that read the same digit rows run on the same XCD.  Grid:
 // ceil(n*(L+1)/8)*8*2 workgroups.
 //
-// ONLY_P: the sums mod P alone (grid ceil(n/8)*8*2), stored centred into
+// PLAIN: TERMS digits, and a plaintext term where m < L.  AHEAD > 2: for calls
+// of at most one workgroup per CU, whose registers are free for more loads in
+// flight (rotation of one ciphertext 28.9 -> 26.9 us).  ONLY_P: the sums mod P alone (grid ceil(n/8)*8*2), stored centred into
 // (-P/2, P/2] as inner_moddown_kernel takes them.
-template <int LOGN, bool PM, bool ONLY_P>
-__global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_kernel(
+template <int LOGN, bool PM, bool ONLY_P, int TERMS, int AHEAD = 2, bool PLAIN = false>
+__global__ __launch_bounds__((1 << LOGN) >> 3, AHEAD > 2 ? 4 : ntt_waves(3)) void inner_intt_kernel(
     InnerArgs g, uint64_t* __restrict__ acc, uint64_t n, const Tw* __restrict__ tw_all,
     const LimbConst* __restrict__ ext) {
   constexpr int LOGE = 3, E = 1 << LOGE, N = 1 << LOGN, T = N / E;
@@ -400,7 +441,10 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_ker
   const int tid = threadIdx.x;
   const LimbConst c = ext[m];
   uint64_t x[E];
-  inner_sums<LOGN, PM>(x, g, i, comp, m, c, tid);
+  if (PLAIN && m < g.L)  // (uniform)
+    inner_sums<LOGN, PM, TERMS + 1, AHEAD>(x, g, i, comp, m, c, tid);
+  else
+    inner_sums<LOGN, PM, TERMS, AHEAD>(x, g, i, comp, m, c, tid);
   ntt_inv_regs<LOGN, LOGE, PM>(x, tw_all + (size_t)m * N, c, lds, tid);
   uint64_t* out = acc + ((i * 2 + comp) * L1 + m) * N;
 #pragma unroll
@@ -414,7 +458,7 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_intt_ker
 // mod q_m and moddown_kernel's pass over them fall away.  b (component 1) is
 // read through the automorphism from the transform's LDS, staged with
 // coalesced loads.  Grid: ceil(n*L/8)*8*2 workgroups.  Signed transforms only.
-template <int LOGN>
+template <int LOGN, int TERMS>
 __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_moddown_kernel(
     InnerArgs g, const uint64_t* __restrict__ acc, uint64_t n, const Tw* __restrict__ tw_all,
     const LimbConst* __restrict__ ext, const uint64_t* ct, uint64_t* out_, uint32_t ginv, KsConst kc,
@@ -432,7 +476,7 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void inner_moddown_
   LimbConst c = ext[m];
   c.pninv = kc.ninv[m], c.pninv_w = kc.ninv_w[m];
   uint64_t x[E];
-  inner_sums<LOGN, true>(x, g, i, comp, m, c, tid);
+  inner_sums<LOGN, true, TERMS>(x, g, i, comp, m, c, tid);
   ntt_inv_regs<LOGN, LOGE, true, true>(x, tw_all + (size_t)m * N, c, lds, tid);  // |x| < 0.9u
   const PmRegs pk = pm_regs(c);
   const uint64_t* xc = acc + ((i * 2 + comp) * L1 + L) * N + tid;
@@ -606,13 +650,32 @@ hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64
   if (blocks > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;  // up to N/8 = 1024 threads
   if (!blocks) return hipSuccess;
   const dim3 grid((uint32_t)blocks);
-#define HECONV_INNER(LN)                                                                                           \
-  if (pm)                                                                                                          \
-    hipLaunchKernelGGL((inner_intt_kernel<LN, true, false>), grid, dim3((1u << LN) / 8), 0, st, g, acc, n, tw_inv, \
-                       ext);                                                                                       \
-  else                                                                                                             \
-    hipLaunchKernelGGL((inner_intt_kernel<LN, false, false>), grid, dim3((1u << LN) / 8), 0, st, g, acc, n,        \
-                       tw_inv, ext)
+  const bool few = blocks <= 256, known = pm && (nd == 2 || nd == 3);
+#define HECONV_INNER_GO(...) \
+  hipLaunchKernelGGL((inner_intt_kernel<__VA_ARGS__>), grid, t, 0, st, g, acc, n, tw_inv, ext)
+#define HECONV_INNER_ND(LN, ND)                      \
+  do {                                               \
+    if (xp && few)                                   \
+      HECONV_INNER_GO(LN, true, false, ND, 8, true); \
+    else if (xp)                                     \
+      HECONV_INNER_GO(LN, true, false, ND, 2, true); \
+    else if (few)                                    \
+      HECONV_INNER_GO(LN, true, false, ND, 8);       \
+    else                                             \
+      HECONV_INNER_GO(LN, true, false, ND, 2);       \
+  } while (0)
+#define HECONV_INNER(LN)                    \
+  do {                                      \
+    const dim3 t((1u << LN) / 8);           \
+    if (!pm)                                \
+      HECONV_INNER_GO(LN, false, false, 0); \
+    else if (!known)                        \
+      HECONV_INNER_GO(LN, true, false, 0);  \
+    else if (nd == 2)                       \
+      HECONV_INNER_ND(LN, 2);               \
+    else                                    \
+      HECONV_INNER_ND(LN, 3);               \
+  } while (0)
   switch (logN) {
     case 10: HECONV_INNER(10); break;
     case 11: HECONV_INNER(11); break;
@@ -621,18 +684,46 @@ hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64
     default: return hipErrorInvalidValue;
   }
 #undef HECONV_INNER
+#undef HECONV_INNER_ND
+#undef HECONV_INNER_GO
   return hipGetLastError();
 }
 
+template <int LOGN, int TERMS>
+static void inner_p_go(const InnerArgs& g, uint64_t* acc, uint64_t n, const Tw* tw_inv, const LimbConst* ext,
+                       hipStream_t st) {
+  hipLaunchKernelGGL((inner_intt_kernel<LOGN, true, true, TERMS>), dim3((uint32_t)((n + 7) / 8 * 8 * 2)),
+                     dim3((1u << LOGN) / 8), 0, st, g, acc, n, tw_inv, ext);
+}
+
+template <int LOGN, int TERMS>
+static void inner_q_go(const InnerArgs& g, uint64_t* acc, uint64_t n, const Tw* tw_inv, const LimbConst* ext,
+                       const uint64_t* ct, uint64_t* out, uint32_t ginv, const KsConst& kc, const uint64_t* addp,
+                       hipStream_t st) {
+  hipLaunchKernelGGL((inner_moddown_kernel<LOGN, TERMS>), dim3((uint32_t)((n * g.L + 7) / 8 * 8 * 2)),
+                     dim3((1u << LOGN) / 8), 0, st, g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp);
+}
+
+// The sums mod P take the digits alone; the others the plaintext term too.
 template <int LOGN>
 static void inner_moddown_go(const InnerArgs& g, uint64_t* acc, uint64_t n, const Tw* tw_inv, const LimbConst* ext,
                              const uint64_t* ct, uint64_t* out, uint32_t ginv, const KsConst& kc, const uint64_t* addp,
                              hipStream_t st) {
-  const dim3 t((1u << LOGN) / 8);
-  hipLaunchKernelGGL((inner_intt_kernel<LOGN, true, true>), dim3((uint32_t)((n + 7) / 8 * 8 * 2)), t, 0, st, g, acc, n,
-                     tw_inv, ext);
-  hipLaunchKernelGGL((inner_moddown_kernel<LOGN>), dim3((uint32_t)((n * g.L + 7) / 8 * 8 * 2)), t, 0, st, g, acc, n,
-                     tw_inv, ext, ct, out, ginv, kc, addp);
+  const uint32_t terms = g.nd + (g.xp ? 1 : 0);
+  if (g.nd == 2)
+    inner_p_go<LOGN, 2>(g, acc, n, tw_inv, ext, st);
+  else if (g.nd == 3)
+    inner_p_go<LOGN, 3>(g, acc, n, tw_inv, ext, st);
+  else
+    inner_p_go<LOGN, 0>(g, acc, n, tw_inv, ext, st);
+  if (terms == 2)
+    inner_q_go<LOGN, 2>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st);
+  else if (terms == 3)
+    inner_q_go<LOGN, 3>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st);
+  else if (terms == 4)
+    inner_q_go<LOGN, 4>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st);
+  else
+    inner_q_go<LOGN, 0>(g, acc, n, tw_inv, ext, ct, out, ginv, kc, addp, st);
 }
 
 hipError_t inner_moddown_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
