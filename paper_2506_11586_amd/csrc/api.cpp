@@ -576,7 +576,7 @@ he_status proto_geom(const he_ctx* c, const he_conv_desc* d, uint32_t B, heconv:
   p.bh = g.bh, p.bw = g.bw, p.nsj = g.nsj, p.S = g.S, p.CB = g.CB, p.O = g.O, p.He = g.He, p.We = g.We;
   p.Ho = (d->H + 2 * d->pad - d->kh) / d->stride + 1, p.Wo = (d->W + 2 * d->pad - d->kw) / d->stride + 1;
   p.step = g.sub ? d->stride : 1, p.ostep = g.sub ? 1 : d->stride;
-  p.pad = (int32_t)d->pad, p.L = c->L, p.N = c->N, p.t = c->t;
+  p.pad = (int32_t)d->pad, p.L = c->L, p.N = c->N, p.t = c->t, p.tmu = c->tlc.mu64;
   return HE_OK;
 }
 

@@ -137,7 +137,7 @@ struct ProtoGeom {
   uint32_t ostep;  // stride-1 output rows/columns per kept output (1 for a strided 1x1 conv, else stride)
   int32_t pad;
   uint32_t L, N;
-  uint64_t t;
+  uint64_t t, tmu;  // tmu = floor(2^64 / t)
 };
 
 // b_l += delta_l * pack(share) mod q_l for in [B][CB][S][2][L][N], share
