@@ -142,13 +142,16 @@ void he_ctx_destroy(he_ctx* ctx);
  * products, two fused multiply-adds, a rounding and a conditional add, all
  * at the full fp64 rate, where the integer path's 32-bit multiplies run at
  * half rate.  0 = always the integer kernels.
- * ks_fused: how key switching and rotation (N <= 2^13) run their steps.
+ * ks_fused: how key switching and rotation run their steps
+ * (modes 1 and 2 at N <= 2^13; at 2^14 see below).
  * 1 = two fused kernels: digit extension (and the automorphism) in the
  * forward transform's load, the inner product with the key in the inverse
  * transform's load.  2 = one kernel extends, transforms and multiplies all
  * digits of a (ciphertext, modulus) pair by the key and stores only the two
  * sums (registers limit it to one workgroup per compute unit).  0 = the
  * steps as separate kernels.  Results are the same words in every mode.
+ * With primes of the signed transforms' form, mode 1 takes a few ciphertexts
+ * (any number at N = 2^14) through three grids of small workgroups instead.
  * ntt_inv_split_below: inverse NTTs of fewer than this many limb
  * polynomials (N = 2^13 and 2^14) run as two grids of 128-thread
  * workgroups, eight per 2^13 points (the stages on the low bits in blocks of

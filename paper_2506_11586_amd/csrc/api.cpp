@@ -738,6 +738,40 @@ he_status ks_tail(const he_ctx* ext, const uint64_t* digits, const uint64_t* ksk
   return s;
 }
 
+// Whether n ciphertexts take the three grids of small workgroups
+// (ks_split.hip, signed transforms) instead of one workgroup per polynomial.
+// By limb transforms, n*(L+1)*(L+2): the latter's kernels take about a whole
+// transform's latency each until their workgroups fill the chip, so that they
+// win from there on; at N = 2^14 they don't exist, and the separate steps lose
+// at every count.  Rotation, us, without -> with:
+//   N = 4096, L = 2:  1 ciphertext 17.3 -> 15.5, 16 (192) 20.1 -> 19.0, 24 (288) 21.5 -> 25.4
+//             L = 1: 32 (192) 20.2 -> 17.9, 40 (240) 21.2 -> 22.2
+//   N = 8192, L = 3:  1 26.2 -> 16.9, 16 (320) 36.0 -> 32.5, 18 (360) 35.9 -> 37.5
+//             L = 1: 48 (288) 33.1 -> 28.9;  L = 2: 24 (288) 32.9 -> 30.5
+//             L = 7:  4 (288) 43.0 -> 31.3
+//   N = 16384, L = 3: 1 23.8 -> 17.7, 64 217 -> 175, 256 889 -> 733
+bool ks_few(const he_ctx* ext, uint64_t n) {
+  if (!ext->ntt_pm || !heconv::ks_split_supported(ext->logN)) return false;
+  const uint64_t transforms = n * ext->L * (ext->L + 1);
+  return ext->logN == 14 || transforms <= (ext->logN == 13 ? 320 : 192);
+}
+
+// One key switch of n ciphertexts ct with the automorphism's inverse exponent
+// ginv, from their coefficients to the switched ciphertexts (by default).
+he_status ks_step(const he_ctx* ext, uint32_t ginv, uint64_t n, const uint64_t* ct, const uint64_t* ksk,
+                  uint64_t* digits, uint64_t* acc, uint64_t* out, const uint64_t* xp, const uint64_t* wp,
+                  uint64_t chain_cts, uint64_t w_stride, const uint64_t* addp, hipStream_t st) {
+  const uint32_t L = ext->L - 1;
+  if (ks_few(ext, n))
+    return dev_err(heconv::ks_split_launch(ext->logN,
+                                           {ct, ksk, digits, acc, out, n, L, ginv, xp, wp, chain_cts, w_stride, addp,
+                                            ext->d_fwd, ext->d_inv, ext->d_lc, ext->ks},
+                                           st));
+  he_status s =
+      dev_err(heconv::modup_ntt_launch(ext->logN, ct, digits, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
+  return s ? s : ks_tail(ext, digits, ksk, acc, n, L, xp, wp, chain_cts, w_stride, ct, out, ginv, addp, st);
+}
+
 he_status ks_run(const he_ctx* ext, uint32_t ginv, uint64_t n, const uint64_t* ct, const uint64_t* ksk, uint64_t* out,
                  uint64_t* work, hipStream_t st, const uint64_t* addp = nullptr) {
   const uint32_t L = ext->L - 1, N = ext->N;
@@ -745,9 +779,8 @@ he_status ks_run(const he_ctx* ext, uint32_t ginv, uint64_t n, const uint64_t* c
   uint64_t* acc = work + n * L * (uint64_t)(L + 1) * N;      // [n][2][L+1][N]
   he_status s = HE_OK;
   const bool fusable = heconv::ks_fwd_supported(ext->logN);
-  if (ext->tune.ks_fused == 1 && fusable) {
-    s = dev_err(heconv::modup_ntt_launch(ext->logN, ct, digits, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
-    return s ? s : ks_tail(ext, digits, ksk, acc, n, L, nullptr, nullptr, 0, 0, ct, out, ginv, addp, st);
+  if (ext->tune.ks_fused == 1 && (fusable || ks_few(ext, n))) {
+    return ks_step(ext, ginv, n, ct, ksk, digits, acc, out, nullptr, nullptr, 0, 0, addp, st);
   } else {
     if (ext->tune.ks_fused == 2 && fusable) {
       s = dev_err(heconv::ks_fwd_launch(ext->logN, ct, ksk, acc, n, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
@@ -953,11 +986,11 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
   for (uint32_t step = 0; step < per; step++) {
     const uint32_t i = per - 1 - step;
     uint64_t* next = groups == 1 && step + 1 == per ? d_out : accb[cur];
-    he_status s = HE_OK;
-    if (prev) s = dev_err(heconv::modup_ntt_launch(ext->logN, prev, digits, nc, L, ginv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
-    if (!s)
-      s = ks_tail(ext, digits, ksk, sums, nc, prev ? L : 0, d_x_ntt, d_w + (uint64_t)i * L * N, n, (uint64_t)per * L * N,
-                  prev, next, ginv, nullptr, st);
+    const uint64_t* w = d_w + (uint64_t)i * L * N;
+    he_status s = prev ? ks_step(ext, ginv, nc, prev, ksk, digits, sums, next, d_x_ntt, w, n, (uint64_t)per * L * N,
+                                 nullptr, st)
+                       : ks_tail(ext, digits, ksk, sums, nc, 0, d_x_ntt, w, n, (uint64_t)per * L * N, nullptr, next,
+                                 ginv, nullptr, st);
     if (s) return s;
     prev = next;
     cur ^= 1;
@@ -970,10 +1003,8 @@ he_status zp_run(const he_ctx* ext, uint32_t g, uint64_t n, const uint64_t* d_x_
   const uint64_t* acc = prev + (uint64_t)(groups - 1) * n * ctw;
   for (uint32_t c = groups - 1; c-- > 0;) {
     uint64_t* next = c == 0 ? d_out : tmp[c & 1];
-    he_status s = dev_err(heconv::modup_ntt_launch(ext->logN, acc, digits, n, L, g2inv, ext->d_fwd, ext->d_lc, ext->ntt_pm, st));
-    if (!s)
-      s = ks_tail(ext, digits, ksk2, sums, n, L, nullptr, nullptr, 0, 0, acc, next, g2inv, prev + (uint64_t)c * n * ctw,
-                  st);
+    he_status s = ks_step(ext, g2inv, n, acc, ksk2, digits, sums, next, nullptr, nullptr, 0, 0,
+                          prev + (uint64_t)c * n * ctw, st);
     if (s) return s;
     acc = next;
   }

@@ -72,6 +72,23 @@ hipError_t inner_moddown_launch(uint32_t logN, const uint64_t* digits, const uin
                                 uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
                                 uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, const uint64_t* ct,
                                 uint64_t* out, uint32_t ginv, const KsConst& kc, const uint64_t* addp, hipStream_t st);
+// Key switching of a few ciphertexts in three grids (ks_split.hip; signed
+// transforms, N = 2^12 .. 2^14): the automorphism, digits, inner product
+// (with the plaintext term of inner_intt_launch), division by P and addend.
+struct KsSplit {
+  const uint64_t *ct, *ksk;
+  uint64_t *digits, *acc, *out;
+  uint64_t n;
+  uint32_t L, ginv;
+  const uint64_t *xp, *wp;
+  uint64_t chain_cts, w_stride;
+  const uint64_t* addp;
+  const Tw *fwd, *inv;
+  const LimbConst* ext;
+  KsConst kc;
+};
+bool ks_split_supported(uint32_t logN);
+hipError_t ks_split_launch(uint32_t logN, const KsSplit& s, hipStream_t st);
 hipError_t galois_key_launch(const uint64_t* work, uint64_t* ksk, uint32_t N, uint32_t L, const LimbConst* ext,
                              hipStream_t st);
 

@@ -17,11 +17,9 @@
 // polynomial's workgroups of both grids run on one XCD when the count
 // allows, so the intermediate stays in that XCD's L2.
 #include "kernels.h"
-#include "ntt_impl.h"
+#include "split_impl.h"
 
 namespace heconv {
-
-constexpr int SPLIT_T = 128;  // threads per workgroup (8 words each)
 
 // Workgroup b -> (limb polynomial, part).  With W = 8 parts and the count a
 // multiple of 8, the parts of polynomial p all have b = p (mod 8).
@@ -70,22 +68,6 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_fwd_split_a(uint64_t* __restrict_
   }
 }
 
-// Remaining stages (bits n-7 .. 0) of one 1024-element block.
-template <int LOGN, int P, bool PM>
-__device__ __forceinline__ void split_b_rest(uint64_t (&x)[8], uint64_t* lds, int tid, const Tw* __restrict__ tw,
-                                             const LimbConst& c, const PmRegs& pk, uint32_t jb) {
-  constexpr int NB = LOGN - 6;  // stages in this grid
-  constexpr int NFULL = NB / 3, REM = NB % 3;
-  if constexpr (P < NFULL || (P == NFULL && REM > 0)) {
-    constexpr int LO = P < NFULL ? NB - 3 * (P + 1) : 0, U0 = P < NFULL ? 0 : 3 - REM;
-    PassTw<LOGN, 3, LO, U0, PM> t;
-    t.load(tid, tw, jb);
-    if constexpr (P > 0) exchange<3, NB - 3 * P, LO>(lds, x, tid);
-    fwd_pass<(P == 0)>(x, t, c, pk);
-    split_b_rest<LOGN, P + 1, PM>(x, lds, tid, tw, c, pk, jb);
-  }
-}
-
 template <int LOGN, bool PM>
 __global__ __launch_bounds__(SPLIT_T) void ntt_fwd_split_b(uint64_t* __restrict__ polys_, uint32_t nlp, uint32_t L,
                                                             const Tw* __restrict__ tw_all,
@@ -120,21 +102,6 @@ __global__ __launch_bounds__(SPLIT_T) void ntt_fwd_split_b(uint64_t* __restrict_
 // inverse in the index v = i*16 + (g - g0), the top one applying N^-1.
 // Values keep the transform's lazy form between the grids (below 3q; PM:
 // signed, below 1.8 * 2^60); the result is canonical.
-template <int LOGN, int P, int PREV, bool PM>
-__device__ __forceinline__ void inv_split_c_rest(uint64_t (&x)[8], uint64_t* lds, int tid,
-                                                 const Tw* __restrict__ tw, const LimbConst& c,
-                                                 const PmRegs& pk, uint32_t jb) {
-  constexpr int NB = LOGN - 6, NFULL = NB / 3, REM = NB % 3;
-  if constexpr (P < NFULL) {
-    constexpr int LO = P < 0 ? 0 : REM + 3 * P, U0 = P < 0 ? 3 - REM : 0;
-    PassTw<LOGN, 3, LO, U0, PM> t;
-    t.load(tid, tw, jb);
-    exchange<3, PREV, LO>(lds, x, tid);
-    inv_pass<false>(x, t, c, pk);
-    inv_split_c_rest<LOGN, P + 1, LO, PM>(x, lds, tid, tw, c, pk, jb);
-  }
-}
-
 template <int LOGN, bool PM>
 __global__ __launch_bounds__(SPLIT_T) void ntt_inv_split_c(uint64_t* __restrict__ polys_, uint32_t nlp, uint32_t L,
                                                             const Tw* __restrict__ tw_all,

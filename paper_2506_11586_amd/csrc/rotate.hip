@@ -20,9 +20,9 @@
 // kernels between them are the separate-steps form, and ks_fwd_kernel the
 // form with both sums kept in registers (tuning ks_fused 0 and 2).
 #include "kernels.h"
+#include "ks_args.h"
 #include "mac_impl.h"
 #include "ntt_impl.h"
-#include "udiv.h"
 
 namespace heconv {
 
@@ -30,17 +30,6 @@ constexpr uint32_t ROT_THREADS = 256;
 
 __device__ __forceinline__ uint64_t red_word(uint64_t x, const LimbConst& c) {
   return csub(reduce64_lazy(x, c.mu64, c.q), c.q);
-}
-
-// Coefficient j of a(X^g) for the row a of N canonical residues mod q:
-// with k = j * g^-1 mod 2N, a_k when k < N, else -a_{k-N}.  ginv = 1 reads
-// the row as it is.
-__device__ __forceinline__ uint64_t perm_load(const uint64_t* __restrict__ row, uint32_t j, uint32_t ginv, uint32_t N,
-                                              uint64_t q) {
-  const uint32_t k = (uint32_t)(((uint64_t)j * ginv) & (2 * N - 1));
-  if (k < N) return row[k];
-  const uint64_t v = row[k - N];
-  return v ? q - v : 0;
 }
 
 // out[r] = in[r](X^g) for every row r of N coefficients; row r is limb
@@ -279,27 +268,10 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void modup_ntt_kern
 // the key row (comp, m) at word io_base + 64*k, plus the plaintext term,
 // reduced once.
 //
-// With a plaintext term (xp, wp non-null; the Z_P multiply-accumulate-rotate
-// step), the sum for a ciphertext modulus m < L also takes
-// xp[i][c][m] * wp[m]: the input ciphertext times a plaintext already
-// multiplied by -P mod q_m.  The term is 0 mod P, so the division by P leaves
-// the rotated ciphertext plus (x * plaintext) exactly.  nd digits are summed
-// (L, or 0 when the rotated ciphertext is zero).  The batch may hold several
-// chains of chain_cts ciphertexts that share the input x but take different
-// weights: ciphertext i uses x[i % chain_cts] and the plaintext at
-// wp + (i / chain_cts) * w_stride.
-//
 // PM: the products of 30-bit halves in three accumulators (at most eight
 // terms: am stays below 2^64) and one short fold, left below 2^60 + 2^54;
 // else 128-bit sums (each product below 2^120) and a full reduction.  TERMS:
 // the number of terms where it is known (0: any).
-struct InnerArgs {
-  const uint64_t *digits, *ksk, *xp, *wp;
-  uint64_t w_stride;
-  UDiv chain;  // by chain_cts
-  uint32_t chain_cts, L, nd;
-};
-
 template <int LOGN, bool PM, int TERMS, int AHEAD = 2>
 __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g, uint64_t i, uint32_t comp, uint32_t m,
                                            const LimbConst& c, int tid) {
@@ -633,13 +605,6 @@ hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits,
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-// (without a plaintext term, or as one chain, every ciphertext is its own)
-static InnerArgs inner_args(const uint64_t* digits, const uint64_t* ksk, const uint64_t* xp, const uint64_t* wp,
-                            uint64_t chain_cts, uint64_t w_stride, uint32_t L, uint32_t nd) {
-  const uint32_t cts = chain_cts && chain_cts < (1ull << 31) ? (uint32_t)chain_cts : 0x7fffffffu;
-  return InnerArgs{digits, ksk, xp, wp, w_stride, udiv_make(cts), cts, L, nd};
 }
 
 hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
