@@ -57,8 +57,10 @@ PAPER_CONTEXT = {
 VALU_PEAK_GIPS = 256 * 2.4  # G full-rate wave64 VALU instructions/s: one per CU per cycle, 256 CUs at 2.4 GHz
 VALU_LANE_OPS_PEAK = 256 * 64 * 2.4e9  # full-rate 32-bit lane operations/s: 256 CUs x 64 lanes x 2.4 GHz
 MAD_RATE_FRAC = 1.0  # v_mad_u64_u32 issues at the full rate on gfx950 (the probe's mad_u64_u32 field: 0.975)
-# VALU instructions of one butterfly in the compiled transforms (the
-# probes' butterfly loops: 672 VALU instructions per 32 butterflies, both)
+# VALU instructions of one butterfly of the unsigned transforms, as compiled
+# (the probes' butterfly loops: 672 VALU instructions per 32 butterflies, both).
+# Primes 2^b - delta with a small delta take the signed transforms, whose
+# butterflies have fewer, so the fractions state the rate in these units.
 BFLY_VALU_INSTS = {"batch_inv": 21, "batch_fwd": 21}
 SCHEDULE_NAMES = {1: "one chain", 2: "two chains", 3: "pipelined in 4 groups", 4: "pipelined in 8 groups"}
 # layer solves (image 0) the oracle recomputes in the CPU-baseline leg

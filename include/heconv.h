@@ -183,9 +183,11 @@ void he_ctx_destroy(he_ctx* ctx);
  * and channels; 0 = each wave its own 64 points.  Measured on the 16-image
  * bottleneck CNN's MAC grid: 98 ms per wave (6x4 tiles), 90 ms on the grid
  * (4x4 per wave, three stages), 88 ms with four stages.
- * Defaults: {3, 3, 512, 0, 0, 0, 1, 160, 1, 1, 128, 3, 0, 1}: 8 words per thread was measured faster
- * than 16 at every count at N = 8192 (768 limb polys: 47.7 against 51.4 us
- * inverse); N = 16384 always uses 16.  The channel pipeline (layer_split)
+ * Defaults: {3, 3, 512, 0, 0, 0, 1, 160, 1, 1, 128, 3, 0, 1} (the split
+ * thresholds 160 and 128 for primes without the signed form): 8 words per
+ * thread was measured faster than 16 at every count at N = 8192 (768 limb
+ * polys, unsigned form: 47.7 against 51.4 us inverse); N = 16384 always uses
+ * 16.  The channel pipeline (layer_split)
  * was measured slower than the plain order on 64->64, 128->128 and
  * 256->256 3x3 layers (141 / 153 us against 127 us on 64->64): the MAC and
  * the transforms compete for the same compute units instead of

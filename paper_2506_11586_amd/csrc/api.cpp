@@ -719,16 +719,20 @@ he_status ks_check(const he_ctx* ext, uint64_t n) {
 // From the transformed digits to the switched ciphertext: inner product,
 // inverse transform, division by P.  With the signed transforms and enough
 // ciphertexts the division rides on the transform (inner_moddown_launch: the
-// sums mod P first, then the rest), else a kernel of its own follows; the
-// sums mod P run alone first, so the rest must fill the chip by itself.
-// Rotation at N = 8192, L = 3, fused against not: 64 ciphertexts 82 against
-// 78 us, 128 131 against 146, 256 282 against 315.
+// sums mod P first, then the rest), else a kernel of its own follows.  The
+// sums mod P run alone first, so the rest must fill the chip by itself: from
+// one workgroup per CU on (N = 2^13, whose workgroups run longer: one and a
+// half).  Rotation, us, division fused against not, by workgroups:
+//   N = 2048, L = 2: 256 21.8 against 22.4, 512 30.1 / 31.9, 2048 65.7 / 76.4
+//   N = 4096, L = 2: 192 30.7 / 31.1, 256 32.3 / 31.8, 512 43.9 / 46.8;
+//             L = 4: 192 37.3 / 30.5, 256 39.0 / 40.3
+//   N = 8192, L = 3: 288 74.2 / 67.4, 384 75.3 / 73.7, 480 82.9 / 91.5, 1536 246 / 287;
+//             L = 2: 256 50.5 / 51.2, 384 66.9 / 71.3
 he_status ks_tail(const he_ctx* ext, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n, uint32_t nd,
                   const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts, uint64_t w_stride, const uint64_t* ct,
                   uint64_t* out, uint32_t ginv, const uint64_t* addp, hipStream_t st) {
   const uint32_t L = ext->L - 1;
-  const uint64_t threads = n * L * 2 * (ext->N / 8);
-  if (ext->ntt_pm && threads >= 256 * 2048)  // 2048 threads a CU
+  if (ext->ntt_pm && n * L * 2 >= (ext->logN == 13 ? 384 : 256))
     return dev_err(heconv::inner_moddown_launch(ext->logN, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride,
                                                 ext->d_inv, ext->d_lc, ct, out, ginv, ext->ks, addp, st));
   he_status s = dev_err(heconv::inner_intt_launch(ext->logN, digits, ksk, acc, n, L, nd, xp, wp, chain_cts, w_stride,

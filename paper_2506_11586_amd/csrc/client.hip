@@ -96,8 +96,11 @@ __global__ __launch_bounds__(CLIENT_THREADS) void encrypt_finish_kernel(const ui
 //  else: src = ct [n][2][L][N]; dst[i][l] = b - a*sk, the phase's residues.
 // Bound by the two transforms; its bytes are the inputs and outputs once (the
 // separate steps moved each polynomial nine times, six of them in passes of
-// their own): 64 encryptions and decryptions at N = 8192, L = 3 in 98 us
-// before, 10 launches.
+// their own): 64 encryptions and decryptions at N = 8192, L = 3 98 us in ten
+// launches before, 55 us in three (30, 25 and decrypt_finish's 7 us).  With 192
+// workgroups, one to a CU, each runs at its own latency; the transforms split
+// over grids of small workgroups promise no better: 16 rotations, 192 forward
+// and 128 inverse transforms with their products, take 32 us so (ks_split.hip).
 template <int LOGN, int LOGE, bool ENC>
 __global__ __launch_bounds__((1 << LOGN) >> LOGE, ntt_waves(LOGE)) void client_product_kernel(
     const uint64_t* __restrict__ src, const uint64_t* __restrict__ sk_ntt, const int64_t* __restrict__ msg,

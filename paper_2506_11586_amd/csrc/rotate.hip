@@ -13,10 +13,15 @@
 //   (moddown_kernel), giving (-A', b - B') under s.
 // A rotation applies the automorphism to a while the digits are read and to
 // b in the last step, so the rotated ciphertext is never stored.
-// By default the steps run as three kernels: modup_ntt_kernel (digit
-// extension in the forward transform's load), inner_intt_kernel (the inner
-// product in the inverse transform's load) and moddown_kernel.  The
-// elementwise modup_kernel and ks_inner_kernel with the library's NTT
+// Forms, by the number of ciphertexts (ks_step in api.cpp):
+//   few: three grids of small workgroups (ks_split.hip);
+//   more: modup_ntt_kernel (digit extension in the forward transform's load),
+//     inner_intt_kernel (the inner product in the inverse transform's load)
+//     and moddown_kernel;
+//   many, signed transforms: modup_ntt_kernel, inner_intt_kernel for the sums
+//     mod P alone, and inner_moddown_kernel (the other sums with the division
+//     by P after their transform, in registers).
+// The elementwise modup_kernel and ks_inner_kernel with the library's NTT
 // kernels between them are the separate-steps form, and ks_fwd_kernel the
 // form with both sums kept in registers (tuning ks_fused 0 and 2).
 #include "kernels.h"
@@ -395,8 +400,9 @@ __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g,
 //
 // PLAIN: TERMS digits, and a plaintext term where m < L.  AHEAD > 2: for calls
 // of at most one workgroup per CU, whose registers are free for more loads in
-// flight (rotation of one ciphertext 28.9 -> 26.9 us).  ONLY_P: the sums mod P alone (grid ceil(n/8)*8*2), stored centred into
-// (-P/2, P/2] as inner_moddown_kernel takes them.
+// flight (rotation of one ciphertext 28.9 -> 26.9 us in this form).  ONLY_P:
+// the sums mod P alone (grid ceil(n/8)*8*2), stored centred into (-P/2, P/2]
+// as inner_moddown_kernel takes them.
 template <int LOGN, bool PM, bool ONLY_P, int TERMS, int AHEAD = 2, bool PLAIN = false>
 __global__ __launch_bounds__((1 << LOGN) >> 3, AHEAD > 2 ? 4 : ntt_waves(3)) void inner_intt_kernel(
     InnerArgs g, uint64_t* __restrict__ acc, uint64_t n, const Tw* __restrict__ tw_all,

@@ -137,7 +137,7 @@ def test_division_by_P_inside_the_transform(g):
     a = synth.uniform_mod(Stream(16, synth.UNIFORM), (2, 3, N), prm_all.q)
     e = Stream(16, synth.ERROR).cbd(2 * N, wl.ETA).reshape(2, N)
     ksk = oracle.galois_key(sk, g, a, e, prm, P)
-    n = 256 * 2048 // (2 * 2 * (N // 8)) + 3  # first size of the fused form, and a remainder
+    n = 64 + 3  # from 64 on the division rides on the transform (256 workgroups of two digits and components)
     ct = synth.uniform_mod(Stream(17, synth.UNIFORM), (n, 2, 2, N), q)
     top = np.array(q, dtype=np.uint64)[:, None] - np.uint64(1)
     ct[0] = top
@@ -147,7 +147,7 @@ def test_division_by_P_inside_the_transform(g):
     dct, out = to_dev(ct), empty_words(ct.size)
     ext.rotate(g, n, dct, dk, out, empty_words(ext.keyswitch_work_words(n)))
     got = to_host(out).reshape(ct.shape)
-    step = 64
+    step = 32
     for i in range(0, n, step):
         m = min(step, n - i)
         part, small = to_dev(ct[i:i + m]), empty_words(ct[i:i + m].size)
