@@ -637,6 +637,21 @@ he_status key_product(const he_ctx* c, uint64_t n, const uint64_t* src, uint64_t
 
 constexpr uint64_t CLIENT_CHUNK = 65535;  // RNS polynomials per launch (grid.y)
 
+// Whether the products of n polynomials with the key run as one kernel
+// (client_product_launch, signed transforms).  Its workgroup takes a whole
+// polynomial through both transforms, at N = 2^14 alone on its CU (36 us and
+// up); a few polynomials there are faster in separate steps, whose transforms
+// are split over the chip.  Encryption / decryption, us, one kernel against
+// the steps, by limb polynomials: 2 40.8/34.9 against 24.2/23.6, 16 41.4/36.4
+// against 25/25, 32 43/38 against 35/34, 40 44.5/39 against 41/39.2, 48 45.0/40
+// against 44.9/42.6.  (In double precision the steps' transforms are not split.)
+bool client_one_kernel(const he_ctx* c, uint64_t n) {
+  const uint64_t polys = n * c->L;
+  const bool split = c->logN == 14 && !(c->fp64_ok && c->tune.ntt_fp64) && polys < c->tune.ntt_split_below &&
+                     polys < c->tune.ntt_inv_split_below;
+  return c->ntt_pm && !(split && polys <= 40);
+}
+
 }  // namespace
 
 he_status he_encrypt(const he_ctx* c, uint64_t n, const int64_t* d_msgs, const uint64_t* d_a, const int64_t* d_err,
@@ -650,7 +665,7 @@ he_status he_encrypt(const he_ctx* c, uint64_t n, const int64_t* d_msgs, const u
   for (uint64_t i0 = 0; i0 < n; i0 += CLIENT_CHUNK) {
     const uint64_t m = n - i0 < CLIENT_CHUNK ? n - i0 : CLIENT_CHUNK;
     uint64_t* ct = d_ct + i0 * 2 * LN;
-    if (c->ntt_pm) {
+    if (client_one_kernel(c, m)) {
       if (he_status s = dev_err(heconv::client_product_launch(
               true, c->logN, d_a + i0 * LN, d_sk_ntt, d_msgs + i0 * c->N, d_err + i0 * c->N, ct, m, c->L, c->tlc, c->d_fwd,
               c->d_inv, c->d_lc, st)))
@@ -677,13 +692,13 @@ he_status he_decrypt(const he_ctx* c, uint64_t n, const uint64_t* d_ct, const ui
   for (uint64_t i0 = 0; i0 < n; i0 += CLIENT_CHUNK) {
     const uint64_t m = n - i0 < CLIENT_CHUNK ? n - i0 : CLIENT_CHUNK;
     const uint64_t* ct = d_ct + i0 * 2 * LN;
-    he_status s = c->ntt_pm ? dev_err(heconv::client_product_launch(false, c->logN, ct, d_sk_ntt, nullptr, nullptr,
-                                                                    d_work, m, c->L, c->tlc, c->d_fwd, c->d_inv,
-                                                                    c->d_lc, st))
-                            : key_product(c, m, ct, 2 * LN, nullptr, d_sk_ntt, d_work, st);
+    const bool one = client_one_kernel(c, m);
+    he_status s = one ? dev_err(heconv::client_product_launch(false, c->logN, ct, d_sk_ntt, nullptr, nullptr, d_work, m,
+                                                              c->L, c->tlc, c->d_fwd, c->d_inv, c->d_lc, st))
+                      : key_product(c, m, ct, 2 * LN, nullptr, d_sk_ntt, d_work, st);
     if (!s)
-      s = dev_err(heconv::decrypt_finish_launch(c->ntt_pm ? nullptr : ct, d_work, d_msgs + i0 * c->N, m, c->N, c->L, c->tlc, c->d_dc,
-                                                c->d_lc, st));
+      s = dev_err(heconv::decrypt_finish_launch(one ? nullptr : ct, d_work, d_msgs + i0 * c->N, m, c->N, c->L, c->tlc,
+                                                c->d_dc, c->d_lc, st));
     if (s) return s;
   }
   return HE_OK;

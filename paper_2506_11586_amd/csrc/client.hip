@@ -14,10 +14,11 @@
 // may be any modulus below 2^62 (a power of two or a prime).
 //
 // With the signed transforms (ntt_impl.h) the product is one kernel:
-// client_product_kernel keeps a polynomial in registers from the a word it
-// reads to the ciphertext word (or the phase word, for decryption) that it
-// writes.  The separate steps (copy, transform, point-wise product, inverse
-// transform, finish) serve the other primes.
+// client_product_kernel keeps a polynomial in registers and LDS (and a few
+// words a thread in scratch) from the a word it reads to the ciphertext word,
+// or the phase word for decryption, that it writes.  The separate steps (copy,
+// transform, point-wise product, inverse transform, finish) serve the other
+// primes, and a few polynomials at N = 2^14 (client_one_kernel in api.cpp).
 #include "kernels.h"
 #include "ntt_impl.h"
 
