@@ -769,6 +769,7 @@ he_status ks_tail(const he_ctx* ext, const uint64_t* digits, const uint64_t* ksk
 //             L = 1: 48 (288) 33.1 -> 28.9;  L = 2: 24 (288) 32.9 -> 30.5
 //             L = 7:  4 (288) 43.0 -> 31.3
 //   N = 16384, L = 3: 1 23.8 -> 17.7, 64 217 -> 175, 256 889 -> 733
+//             L = 1: 8 29.8 -> 18.3, 128 118 -> 93;  L = 7: 8 107 -> 89, 128 1590 -> 1403
 bool ks_few(const he_ctx* ext, uint64_t n) {
   if (!ext->ntt_pm || !heconv::ks_split_supported(ext->logN)) return false;
   const uint64_t transforms = n * ext->L * (ext->L + 1);

@@ -414,11 +414,14 @@ __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g,
 // two workgroups that read the same digit rows run on the same XCD.  Grid:
 // ceil(n*(L+1)/8)*8*2 workgroups.
 //
-// PLAIN: TERMS digits, and a plaintext term where m < L.  AHEAD > 2: for calls
-// of at most one workgroup per CU, whose registers are free for more loads in
-// flight (rotation of one ciphertext 28.9 -> 26.9 us in this form).  ONLY_P:
-// the sums mod P alone (grid ceil(n/8)*8*2), stored centred into (-P/2, P/2]
-// as inner_moddown_kernel takes them.
+// PLAIN: TERMS digits, and a plaintext term where m < L.  AHEAD > 2, for calls
+// of at most one workgroup per CU: more loads in flight, in the registers that
+// other workgroups would need.  It gains where a workgroup has few waves: a Z_P
+// call of 8 diagonals on 8 ciphertexts, L = 3, at N = 1024 105 -> 101 us (two
+// steps ahead -> eight), at N = 2048 119 -> 117; at N = 4096 it lost (16
+// ciphertexts 179 -> 180, L = 2 178 -> 180) and at N = 8192 it changed nothing.
+// ONLY_P: the sums mod P alone (grid ceil(n/8)*8*2), stored centred into
+// (-P/2, P/2] as inner_moddown_kernel takes them.
 template <int LOGN, bool PM, bool ONLY_P, int TERMS, int AHEAD = 2, bool PLAIN = false>
 __global__ __launch_bounds__((1 << LOGN) >> 3, AHEAD > 2 ? 4 : ntt_waves(3)) void inner_intt_kernel(
     InnerArgs g, uint64_t* __restrict__ acc, uint64_t n, const Tw* __restrict__ tw_all,
@@ -629,6 +632,35 @@ hipError_t modup_ntt_launch(uint32_t logN, const uint64_t* ct, uint64_t* digits,
   return hipGetLastError();
 }
 
+template <int LOGN, bool PM, int ND, int AHEAD = 2, bool PLAIN = false>
+static void inner_go(const InnerArgs& g, uint32_t blocks, uint64_t* acc, uint64_t n, const Tw* tw_inv,
+                     const LimbConst* ext, hipStream_t st) {
+  hipLaunchKernelGGL((inner_intt_kernel<LOGN, PM, false, ND, AHEAD, PLAIN>), dim3(blocks), dim3((1u << LOGN) / 8), 0, st,
+                     g, acc, n, tw_inv, ext);
+}
+
+template <int LOGN, int ND>
+static void inner_nd_go(const InnerArgs& g, uint32_t blocks, uint64_t* acc, uint64_t n, const Tw* tw_inv,
+                        const LimbConst* ext, hipStream_t st) {
+  if constexpr (LOGN <= 11) {
+    if (blocks <= 256) {  // at most one workgroup per CU
+      if (g.xp) return inner_go<LOGN, true, ND, 8, true>(g, blocks, acc, n, tw_inv, ext, st);
+      return inner_go<LOGN, true, ND, 8>(g, blocks, acc, n, tw_inv, ext, st);
+    }
+  }
+  if (g.xp) return inner_go<LOGN, true, ND, 2, true>(g, blocks, acc, n, tw_inv, ext, st);
+  inner_go<LOGN, true, ND>(g, blocks, acc, n, tw_inv, ext, st);
+}
+
+template <int LOGN>
+static void inner_intt_go(bool pm, const InnerArgs& g, uint32_t blocks, uint64_t* acc, uint64_t n, const Tw* tw_inv,
+                          const LimbConst* ext, hipStream_t st) {
+  if (!pm) return inner_go<LOGN, false, 0>(g, blocks, acc, n, tw_inv, ext, st);
+  if (g.nd == 2) return inner_nd_go<LOGN, 2>(g, blocks, acc, n, tw_inv, ext, st);
+  if (g.nd == 3) return inner_nd_go<LOGN, 3>(g, blocks, acc, n, tw_inv, ext, st);
+  inner_go<LOGN, true, 0>(g, blocks, acc, n, tw_inv, ext, st);
+}
+
 hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64_t* ksk, uint64_t* acc, uint64_t n,
                              uint32_t L, uint32_t nd, const uint64_t* xp, const uint64_t* wp, uint64_t chain_cts,
                              uint64_t w_stride, const Tw* tw_inv, const LimbConst* ext, bool pm, hipStream_t st) {
@@ -636,43 +668,13 @@ hipError_t inner_intt_launch(uint32_t logN, const uint64_t* digits, const uint64
   const uint64_t blocks = (n * (L + 1) + 7) / 8 * 8 * 2;
   if (blocks > grid_max_blocks(1024)) return hipErrorInvalidConfiguration;  // up to N/8 = 1024 threads
   if (!blocks) return hipSuccess;
-  const dim3 grid((uint32_t)blocks);
-  const bool few = blocks <= 256, known = pm && (nd == 2 || nd == 3);
-#define HECONV_INNER_GO(...) \
-  hipLaunchKernelGGL((inner_intt_kernel<__VA_ARGS__>), grid, t, 0, st, g, acc, n, tw_inv, ext)
-#define HECONV_INNER_ND(LN, ND)                      \
-  do {                                               \
-    if (xp && few)                                   \
-      HECONV_INNER_GO(LN, true, false, ND, 8, true); \
-    else if (xp)                                     \
-      HECONV_INNER_GO(LN, true, false, ND, 2, true); \
-    else if (few)                                    \
-      HECONV_INNER_GO(LN, true, false, ND, 8);       \
-    else                                             \
-      HECONV_INNER_GO(LN, true, false, ND, 2);       \
-  } while (0)
-#define HECONV_INNER(LN)                    \
-  do {                                      \
-    const dim3 t((1u << LN) / 8);           \
-    if (!pm)                                \
-      HECONV_INNER_GO(LN, false, false, 0); \
-    else if (!known)                        \
-      HECONV_INNER_GO(LN, true, false, 0);  \
-    else if (nd == 2)                       \
-      HECONV_INNER_ND(LN, 2);               \
-    else                                    \
-      HECONV_INNER_ND(LN, 3);               \
-  } while (0)
   switch (logN) {
-    case 10: HECONV_INNER(10); break;
-    case 11: HECONV_INNER(11); break;
-    case 12: HECONV_INNER(12); break;
-    case 13: HECONV_INNER(13); break;
+    case 10: inner_intt_go<10>(pm, g, (uint32_t)blocks, acc, n, tw_inv, ext, st); break;
+    case 11: inner_intt_go<11>(pm, g, (uint32_t)blocks, acc, n, tw_inv, ext, st); break;
+    case 12: inner_intt_go<12>(pm, g, (uint32_t)blocks, acc, n, tw_inv, ext, st); break;
+    case 13: inner_intt_go<13>(pm, g, (uint32_t)blocks, acc, n, tw_inv, ext, st); break;
     default: return hipErrorInvalidValue;
   }
-#undef HECONV_INNER
-#undef HECONV_INNER_ND
-#undef HECONV_INNER_GO
   return hipGetLastError();
 }
 

@@ -143,14 +143,16 @@ def test_rotation_in_every_form(L, n):
     assert np.array_equal(outs[0][0][ends], want)
 
 
-def test_zp_at_the_served_size():
-    """N = 8192, three 60-bit primes, eight chains of eight inputs (64
-    ciphertexts in a step): each input as it comes out alone, where the chains
-    take the small grids."""
+@pytest.mark.parametrize("n8,L,n,G", [(8192, 3, 8, 8), (8192, 3, 8, 4), (4096, 2, 9, 4), (2048, 2, 10, 4)])
+def test_zp_at_served_sizes(n8, L, n, G):
+    """64-bit words of larger rings: n inputs through G chains at once (the
+    division inside from 64 ciphertexts at N = 8192 on, else the plain inner
+    product), each input as it comes out alone, where N >= 4096 takes the small
+    grids."""
     require_gpu()
     ensure_built()
     from paper_2506_11586_amd import heconv
-    n8, L, n, G, per = 8192, 3, 8, 8, 3
+    per = 3
     q = heconv.gen_primes(n8, 60, L + 1)
     ext = heconv.Context(n8, q)
     x = synth.uniform_mod(Stream(211, synth.UNIFORM), (n, 2, L, n8), q[:L])
