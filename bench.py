@@ -57,11 +57,12 @@ PAPER_CONTEXT = {
 VALU_PEAK_GIPS = 256 * 2.4  # G full-rate wave64 VALU instructions/s: one per CU per cycle, 256 CUs at 2.4 GHz
 VALU_LANE_OPS_PEAK = 256 * 64 * 2.4e9  # full-rate 32-bit lane operations/s: 256 CUs x 64 lanes x 2.4 GHz
 MAD_RATE_FRAC = 1.0  # v_mad_u64_u32 issues at the full rate on gfx950 (the probe's mad_u64_u32 field: 0.975)
-# VALU instructions of one butterfly of the unsigned transforms, as compiled
-# (the probes' butterfly loops: 672 VALU instructions per 32 butterflies, both).
-# Primes 2^b - delta with a small delta take the signed transforms, whose
-# butterflies have fewer, so the fractions state the rate in these units.
+# VALU instructions of one butterfly as compiled, counted in the probes' loops:
+# of the general transforms (672 per 32 butterflies, both directions) and of the
+# signed ones, which primes 2^b - delta with a small delta take (per 24, their
+# reductions included: 296 inverse, 272 forward)
 BFLY_VALU_INSTS = {"batch_inv": 21, "batch_fwd": 21}
+BFLY_VALU_INSTS_SIGNED = {"batch_inv": 296 / 24, "batch_fwd": 272 / 24}
 SCHEDULE_NAMES = {1: "one chain", 2: "two chains", 3: "pipelined in 4 groups", 4: "pipelined in 8 groups"}
 # layer solves (image 0) the oracle recomputes in the CPU-baseline leg
 ORACLE_SAMPLE_LAYERS = [0, 2, 3, 12, 14, 16, 25, 26, 29, 44, 45, 48]
@@ -109,6 +110,16 @@ def kernel_sources_hash() -> str:
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(f.encode() + fh.read())
     return h.hexdigest()[:16]
+
+
+def signed_form(q) -> bool:
+    """Whether a context with these primes takes the signed transforms: every
+    one 2^b - delta, 34 <= b <= 60, with delta < 2^24 and delta * 2^(60-b) < 2^31."""
+    def ok(v):
+        b = v.bit_length()
+        delta = (1 << b) - v
+        return 34 <= b <= 60 and delta < 1 << 24 and delta << (60 - b) < 1 << 31
+    return all(ok(int(v)) for v in q)
 
 
 def load_counters(kernel: str, workload: str):
@@ -692,7 +703,7 @@ def run_bottleneck_main(torch, heconv, args, probes):
         kavg[k]["alg"] = alg[k]
         kavg[k]["GBps"] = round(alg[k]["bytes"] / t / 1e9, 1)
     roofline, roofline_mac, roofline_hbm, ntt_roof = headline_rooflines(
-        kavg, alg, bt.mac_form, probes, lambda k: load_traffic(k, cfg["name"]))
+        kavg, alg, bt.mac_form, probes, lambda k: load_traffic(k, cfg["name"]), signed_form(ctx.q))
     resident = sum(t.numel() * 8 for t in wntts + ins + outs) / 2 ** 30
     res = {
         "metric": METRIC,
@@ -738,12 +749,13 @@ def run_bottleneck_main(torch, heconv, args, probes):
     return res, pending
 
 
-def headline_rooflines(kavg, alg, form, probes, traffic):
+def headline_rooflines(kavg, alg, form, probes, traffic, signed=False):
     """The bottleneck batch's rooflines from its per-grid durations (kavg:
     ms_per_pass and avg_ms_per_launch per grid), algorithmic work (alg), the
-    batch's MAC form, the VALU probes (or None) and a traffic lookup by grid
-    name.  Returns (roofline, roofline_mac, roofline_hbm, {grid: roofline})
-    for the transforms; roofline is the longest grid's."""
+    batch's MAC form, the VALU probes (or None), a traffic lookup by grid name,
+    and whether the primes take the signed transforms.  Returns (roofline,
+    roofline_mac, roofline_hbm, {grid: roofline}) for the transforms; roofline
+    is the longest grid's."""
     mac_kernel = ("batch_mac_grid_kernel (streamed MAC, 2x2 wave grid)" if form["grid"] else
                   "batch_mac_stream_kernel (streamed MAC)" if form["lds"] >= 2 else "batch_mac_kernel")
     # the MAC at 16 images is bound by integer multiply-adds: each modmul-add
@@ -769,17 +781,18 @@ def headline_rooflines(kavg, alg, form, probes, traffic):
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(mac_gbps / HBM_PEAK_GBS, 4)}
     # the transforms are bound by integer VALU issue: the peak is the chip's
     # full-rate lane operations over the VALU instructions of one butterfly
-    # as compiled (21 in either direction)
+    # as compiled
+    insts = BFLY_VALU_INSTS_SIGNED if signed else BFLY_VALU_INSTS
     ntt_roof = {}
     for k, kname, mix_key in (("batch_inv", "batch_inv_kernel (inverse NTTs)", "intt_mix"),
                               ("batch_fwd", "batch_fwd_kernel (forward NTTs)", "ntt_mix")):
         t = kavg[k]["ms_per_pass"] * 1e-3
         bfly = alg[k]["modmuls"] / t / 1e9
-        peak_b = VALU_LANE_OPS_PEAK / BFLY_VALU_INSTS[k] / 1e9
+        peak_b = VALU_LANE_OPS_PEAK / insts[k] / 1e9
         r = {"bound": "alu", "kernel": kname, "achieved": round(bfly, 1), "peak": round(peak_b, 1),
              "unit": "G butterflies/s", "frac": round(bfly / peak_b, 4), "traffic": traffic(k),
-             "peak_derivation": f"256 CUs x 64 lanes x 2.4 GHz / {BFLY_VALU_INSTS[k]} VALU instructions per "
-                                "butterfly (compiled)",
+             "peak_derivation": f"256 CUs x 64 lanes x 2.4 GHz / {insts[k]:.3g} VALU instructions per "
+                                f"butterfly of the {'signed' if signed else 'general'} transforms (compiled)",
              "avg_launch_ms": round(kavg[k]["avg_ms_per_launch"], 4)}
         if probes:
             ceil = probes[mix_key]["rate"] / 1e9

@@ -12,15 +12,20 @@
 //                        (30-bit splits, four multiply-adds per product into
 //                        three accumulators, one carry per 8 blocks),
 //                        products/s
-//  HE_PROBE_INTT_MIX     the inverse transform's butterfly (lazy sum below 3q,
-//                        mul_shoup_2q of the difference), butterflies/s
-//  HE_PROBE_NTT_MIX      the forward transform's butterfly, butterflies/s
+//  HE_PROBE_INTT_MIX     the inverse transform's butterfly in the form of the
+//                        context's primes (signed: inv_pass with its
+//                        reductions; else lazy sum below 3q and mul_shoup_2q
+//                        of the difference), butterflies/s
+//  HE_PROBE_NTT_MIX      the forward transform's butterfly likewise (signed:
+//                        fwd_pass, reducing once in six stages),
+//                        butterflies/s
 #include <hip/hip_runtime.h>
 
 #include "ctx.h"
 #include "heconv_probe.h"
 #include "mac_impl.h"
 #include "modarith.h"
+#include "ntt_impl.h"
 
 namespace heconv {
 namespace {
@@ -165,6 +170,38 @@ __global__ __launch_bounds__(PROBE_THREADS) void probe_mac_kernel(const uint64_t
   out[t] = s;
 }
 
+// Two full passes (24 butterflies) per thread and trip of the signed transforms,
+// one factor in registers for all; the values stay in the passes' bounds.  VALU
+// instructions of the loop: 296 inverse, 272 forward.
+template <bool INVERSE>
+__global__ __launch_bounds__(PROBE_THREADS) void probe_pass_kernel(const uint64_t* __restrict__ seed, uint64_t* out,
+                                                                   uint32_t iters, const LimbConst* __restrict__ lcs) {
+  const uint32_t t = blockIdx.x * PROBE_THREADS + threadIdx.x;
+  const LimbConst c = lcs[0];
+  const PmRegs pk = pm_regs(c);
+  uint64_t x[8];
+#pragma unroll
+  for (int i = 0; i < 8; i++) x[i] = (seed[(threadIdx.x + i) & 63] + t) % c.q;
+  TwP w = c.pninv;
+  asm volatile("" : "+v"(w.w0), "+v"(w.w1), "+v"(w.v0), "+v"(w.v1));
+  PassTw<13, 3, 4, 0, true> tw;
+#pragma unroll
+  for (int i = 0; i < 7; i++) tw.t[i] = w;
+  for (uint32_t it = 0; it < iters; it++) {
+    if (INVERSE) {
+      inv_pass<false>(x, tw, c, pk);
+      inv_pass<false>(x, tw, c, pk);
+    } else {
+      fwd_pass<true>(x, tw, c, pk);
+      fwd_pass<false>(x, tw, c, pk);
+    }
+  }
+  uint64_t s = 0;
+#pragma unroll
+  for (int i = 0; i < 8; i++) s ^= x[i];
+  out[t] = s;
+}
+
 // Eight independent butterflies per thread, operands and twiddles in
 // registers; the values stay in the transforms' lazy ranges.
 template <bool INVERSE>
@@ -199,6 +236,15 @@ __global__ __launch_bounds__(PROBE_THREADS) void probe_bfly_kernel(const uint64_
 #pragma unroll
   for (int i = 0; i < 16; i++) s ^= x[i];
   out[t] = s;
+}
+
+template <bool INVERSE>
+void bfly_launch(bool pm, uint32_t blocks, hipStream_t st, const uint64_t* seed, uint64_t* out, uint32_t iters,
+                 const LimbConst* lc) {
+  if (pm)
+    hipLaunchKernelGGL(probe_pass_kernel<INVERSE>, dim3(blocks), dim3(PROBE_THREADS), 0, st, seed, out, iters, lc);
+  else
+    hipLaunchKernelGGL(probe_bfly_kernel<INVERSE>, dim3(blocks), dim3(PROBE_THREADS), 0, st, seed, out, iters, lc);
 }
 
 }  // namespace
@@ -247,15 +293,13 @@ extern "C" he_status he_probe_valu(const he_ctx* ctx, uint32_t which, uint32_t i
         break;
       case HE_PROBE_INTT_MIX:
         if (!lc) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(probe_bfly_kernel<true>, dim3(blocks), dim3(PROBE_THREADS), 0, st, d_seed, d_out, iters,
-                           lc);
-        per_thread_iter = (PROBE_UNROLL / 4) * 8;
+        bfly_launch<true>(ctx->ntt_pm, blocks, st, d_seed, d_out, iters, lc);
+        per_thread_iter = ctx->ntt_pm ? 24 : (PROBE_UNROLL / 4) * 8;
         break;
       case HE_PROBE_NTT_MIX:
         if (!lc) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(probe_bfly_kernel<false>, dim3(blocks), dim3(PROBE_THREADS), 0, st, d_seed, d_out, iters,
-                           lc);
-        per_thread_iter = (PROBE_UNROLL / 4) * 8;
+        bfly_launch<false>(ctx->ntt_pm, blocks, st, d_seed, d_out, iters, lc);
+        per_thread_iter = ctx->ntt_pm ? 24 : (PROBE_UNROLL / 4) * 8;
         break;
       default:
         return hipErrorInvalidValue;
