@@ -136,22 +136,26 @@ void he_ctx_destroy(he_ctx* ctx);
  * but 16.9 against 15.6 for 192.  (Contexts whose primes are all 2^b - delta
  * with a small delta start with 0, or 80 at N = 2^14, for this field and
  * ntt_inv_split_below: their one-grid transforms are faster.)
- * ntt_fp64: 1 = when every q_l < 2^50, every transform of the library
- * (except the batch executor's and the fused kernel's) runs in double
- * precision: residues are exact doubles and a modular product is two
- * products, two fused multiply-adds, a rounding and a conditional add, all
- * at the full fp64 rate, where the integer path's 32-bit multiplies run at
- * half rate.  0 = always the integer kernels.
- * ks_fused: how key switching and rotation run their steps
- * (modes 1 and 2 at N <= 2^13; at 2^14 see below).
- * 1 = two fused kernels: digit extension (and the automorphism) in the
- * forward transform's load, the inner product with the key in the inverse
- * transform's load.  2 = one kernel extends, transforms and multiplies all
- * digits of a (ciphertext, modulus) pair by the key and stores only the two
- * sums (registers limit it to one workgroup per compute unit).  0 = the
- * steps as separate kernels.  Results are the same words in every mode.
- * With primes of the signed transforms' form, mode 1 takes a few ciphertexts
- * (any number at N = 2^14) through three grids of small workgroups instead.
+ * ntt_fp64: 1 = when every q_l < 2^50, the transforms that run as kernels of
+ * their own (he_ntt_fwd and he_ntt_inv, layers, encoding of weights, keys and
+ * slots, and the separate steps of key switching and of the client; not the
+ * batch executor's, he_zp_encode_plain's or a fused kernel's) run in double
+ * precision: residues are exact doubles and a modular product is two products,
+ * two fused multiply-adds, a rounding and an addition, all at the full fp64
+ * rate, where the integer path's 32-bit multiplies run at half rate.
+ * 0 = always the integer kernels.
+ * ks_fused: how key switching and rotation run their steps.  0 = as separate
+ * kernels.  1 = fused.  With primes of the signed transforms' form, by the
+ * number of ciphertexts: a few (any number at N = 2^14) through three grids
+ * of small workgroups; more as two kernels (digit extension and the
+ * automorphism in the forward transform's load, the inner product with the
+ * key in the inverse transform's load) and the division by P; many with that
+ * division inside the inverse transform, too, after the sums mod P.  With
+ * other primes, the two kernels and the division by P at N <= 2^13, the
+ * separate steps at 2^14.  2 = one kernel extends, transforms and multiplies
+ * all digits of a (ciphertext, modulus) pair by the key and stores only the
+ * two sums (registers limit it to one workgroup per compute unit; N <= 2^13,
+ * the separate steps at 2^14).  Results are the same words in every mode.
  * ntt_inv_split_below: inverse NTTs of fewer than this many limb
  * polynomials (N = 2^13 and 2^14) run as two grids of 128-thread
  * workgroups, eight per 2^13 points (the stages on the low bits in blocks of

@@ -92,16 +92,18 @@ __global__ __launch_bounds__(CLIENT_THREADS) void encrypt_finish_kernel(const ui
 
 // a*sk for limb l of polynomial i, and what follows it, by one workgroup:
 // forward transform, product with the transformed key (three sums of 30-bit
-// halves and a short fold), inverse transform, all in registers and LDS.
+// halves and a short fold) and inverse transform without a pass through memory.
 //  ENC: src = a [n][L][N]; ct[i][0] = a, ct[i][1] = a*sk + delta*(m mod t) + e.
 //  else: src = ct [n][2][L][N]; dst[i][l] = b - a*sk, the phase's residues.
 // Bound by the two transforms; its bytes are the inputs and outputs once (the
 // separate steps moved each polynomial nine times, six of them in passes of
 // their own): 64 encryptions and decryptions at N = 8192, L = 3 98 us in ten
-// launches before, 55 us in three (30, 25 and decrypt_finish's 7 us).  With 192
-// workgroups, one to a CU, each runs at its own latency; the transforms split
-// over grids of small workgroups promise no better: 16 rotations, 192 forward
-// and 128 inverse transforms with their products, take 32 us so (ks_split.hip).
+// launches before, 55 us in three (a profiler times the kernels alone at 30, 25
+// and decrypt_finish's 7 us).  With 192 workgroups, one to a CU, each runs at its
+// own latency; the transforms split over grids of small workgroups promise no
+// better: 16 rotations, 192 forward and 128 inverse transforms with their
+// products, take 32 us so (ks_split.hip).  The bound of two workgroups a CU
+// leaves 10 registers a lane spilled at N = 8192 (3 at 4096, 11 at 16384).
 template <int LOGN, int LOGE, bool ENC>
 __global__ __launch_bounds__((1 << LOGN) >> LOGE, ntt_waves(LOGE)) void client_product_kernel(
     const uint64_t* __restrict__ src, const uint64_t* __restrict__ sk_ntt, const int64_t* __restrict__ msg,

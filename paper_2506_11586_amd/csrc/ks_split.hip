@@ -13,8 +13,9 @@
 // few ciphertexts, and each of its three kernels then takes one whole
 // transform's latency; here a ciphertext at N = 8192, L = 3 is 96, 32 and 48
 // workgroups, and each grid takes half a transform's: rotation of one 26.2 ->
-// 16.9 us (grids 4.7, 7.8 and 5.6 us; each waits for the words that the last
-// one stored, then runs at one wave per SIMD, bound by its own issue rate).
+// 16.9 us (the grids alone, as a profiler times them, 4.7, 7.8 and 5.6 us; each
+// waits for the words that the last one stored, then runs at one wave per SIMD,
+// bound by its own issue rate).
 // With all of a block's twiddles loaded before its first pass (252 VGPRs) it
 // was no faster, and 16 ciphertexts slower (34.0 against 32.6 us).
 #include "ks_args.h"

@@ -277,11 +277,15 @@ __host__ __device__ __forceinline__ uint64_t fold30_pm(uint64_t a00, uint64_t a0
 }
 
 // The same fold for three accumulators, T = a00 + am*2^30 + a11*2^60 (am
-// takes both cross products of 30-bit halves): exact for a00, am < 2^64 and
-// a11 < 2^63, which eight blocks of products (a00, a11 one per block, am
-// two) on top of a carried value below 2^60 + 2^45 in a00 satisfy.  CANON:
-// the result in [0, q); else X in [0, 2^60 + 2^45), congruent to T, which
-// is all a carried value needs.
+// takes both cross products of 30-bit halves), with 2^60 = delta mod q: for
+// q = 2^60 - delta, or the d60 = d * 2^(60-b) < 2^31 of q = 2^b - d, d < 2^24.
+// Exact for eight blocks of products of residues below 2^b (a00, a11 one per
+// block, am two) on top of a carried value below 2^60 + 2^52 in a00, where
+//   V < 2^(2b-57) + 2^(b-26) + 16, so (V >> 32) * delta < 2^(b-5) <= 2^55
+// (delta < 2^(84-b)), and the low word's product is below 2^63.  CANON (only
+// for q = 2^60 - delta): the result in [0, q); else X in [0, 2^60 + 2^52),
+// congruent to T, which is all a carried value needs.  With delta < 2^20 as
+// the MAC's 60-bit primes have it, X < 2^60 + 2^45.
 template <bool CANON>
 __host__ __device__ __forceinline__ uint64_t fold3_pm(uint64_t a00, uint64_t am, uint64_t a11, uint32_t delta,
                                                       uint32_t two30) {
@@ -290,11 +294,11 @@ __host__ __device__ __forceinline__ uint64_t fold3_pm(uint64_t a00, uint64_t am,
   const uint64_t a60 = ((uint64_t)(a_hi & M28) << 32) | a_lo;
   const uint64_t Lv = (uint64_t)((uint32_t)am & M30) * two30 + a60;                 // < 2^61
   const uint64_t V = a11 + (am >> 30) + (a_hi >> 28);                               // < 2^64
-  const uint64_t W1 = (uint64_t)(uint32_t)V * delta + Lv;                           // < 2^62
-  const uint64_t P = (uint64_t)(uint32_t)(V >> 32) * delta + (uint32_t)(W1 >> 32);  // W >> 32, < 2^53
-  const uint32_t wh = funnel32((uint32_t)(P >> 32), (uint32_t)P, 28);               // W >> 60, < 2^25
+  const uint64_t W1 = (uint64_t)(uint32_t)V * delta + Lv;                           // < 2^63 + 2^61
+  const uint64_t P = (uint64_t)(uint32_t)(V >> 32) * delta + (uint32_t)(W1 >> 32);  // W >> 32, < 2^55 + 2^33
+  const uint32_t wh = funnel32((uint32_t)(P >> 32), (uint32_t)P, 28);               // W >> 60, < 2^27 + 32
   const uint64_t wl = ((uint64_t)((uint32_t)P & M28) << 32) | (uint32_t)W1;          // W mod 2^60
-  const uint64_t X = (uint64_t)wh * delta + wl;                                     // < 2^60 + 2^45
+  const uint64_t X = (uint64_t)wh * delta + wl;                                     // < 2^60 + 2^52
   if (!CANON) return X;
   const uint32_t ge = (uint32_t)((X + delta) >> 60);                                // X >= q
   const uint64_t Z = (uint64_t)ge * delta + X;
@@ -327,10 +331,7 @@ enum MacFold {
   MAC_FOLD_PM = 2    // every q of the signed transforms' form: fold3_pm with 2^60 = d60, then pm_canon
 };
 
-// MAC_FOLD_PM: with q < 2^b the halves' products are smaller as d60 is
-// larger, so that V*d60 of fold3_pm stays below 2^87 and its result below
-// 2^60 + 2^52 for any b; eight more blocks fit on top of it as they do on
-// 2^60 + 2^45.
+// MAC_FOLD_PM: fold3_pm with d60, whose bounds hold for every b.
 template <int F, bool CANON>
 __host__ __device__ __forceinline__ uint64_t mac_fold(uint64_t a00, uint64_t am, uint64_t a11, const LimbConst& c) {
   if constexpr (F == MAC_FOLD_60) {

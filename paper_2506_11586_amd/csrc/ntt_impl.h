@@ -63,11 +63,6 @@ __device__ __forceinline__ int block_of(int tid) {
     return tid >> LO;
 }
 
-// A forward value (below 6q) brought to [0, q).
-__device__ __forceinline__ uint64_t fwd_canon(uint64_t x, const LimbConst& c) {
-  return canon_below6q(x, c.neg3q, c.neg2q, c.negq);
-}
-
 // Place of the twiddle that a thread of block `high` reads as the g-th of a
 // pass's stage u, stage s of the transform.
 template <int TLOGN>

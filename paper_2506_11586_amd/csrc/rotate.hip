@@ -276,7 +276,9 @@ __global__ __launch_bounds__((1 << LOGN) >> 3, ntt_waves(3)) void modup_ntt_kern
 // PM: the products of 30-bit halves in three accumulators (at most eight
 // terms: am stays below 2^64) and one short fold, left below 2^60 + 2^54;
 // else 128-bit sums (each product below 2^120) and a full reduction.  TERMS:
-// the number of terms where it is known (0: any).
+// the number of terms where it is known (0: any; with the signed transforms
+// these bodies spill 7 to 11 registers a lane at the bound of two workgroups a
+// CU, and wait for each term's words).
 template <int LOGN, bool PM, int TERMS, int AHEAD = 2>
 __device__ __forceinline__ void inner_sums(uint64_t (&x)[8], const InnerArgs& g, uint64_t i, uint32_t comp, uint32_t m,
                                            const LimbConst& c, int tid) {
